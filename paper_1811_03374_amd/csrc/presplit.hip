@@ -427,17 +427,19 @@ constexpr int kBlock = 256;                     // fibers per block of k_validat
 // groups of lanes. Bound by memory where most ends are clear (68 bytes a
 // fiber): 800,000 hair segments, 5 % of them hooked, take 24 us (2.3 TB/s)
 // and took 1317 us with every end searched by its own lane. The excesses
-// themselves (EXCESS) need every search.
+// themselves (EXCESS) need every search, one lane per end.
 template <bool EXCESS>
 __global__ __launch_bounds__(kBlock) void k_validate(const float *F, int64_t fs, int64_t n, int32_t *mask,
                                                      float *excess)
 {
-    __shared__ int s_mask[kBlock], s_queue[2 * kBlock], s_full[kBlock], s_n[2];
+    constexpr int kOwn = EXCESS ? kBlock / 2 : kBlock;       // fibers of a block
+    __shared__ int s_mask[kOwn], s_queue[kBlock], s_full[kBlock], s_n[2];
     const int lane = (int)threadIdx.x;
-    const int64_t first = (int64_t)blockIdx.x * kBlock, i = first + lane;
+    const int64_t first = (int64_t)blockIdx.x * kOwn, i = first + lane;
+    const bool own = lane < kOwn && i < n;
     if (lane < 2) s_n[lane] = 0;
     __syncthreads();
-    if (i < n) {
+    if (own) {
         Q16 q;
         load_fiber(F, fs, i, q);
         if (!finite_fiber(q)) {
@@ -483,7 +485,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(const float *F, int64_t fs,
         }
         __syncthreads();
     }
-    if (i < n) mask[i] = s_mask[lane];
+    if (own) mask[i] = s_mask[lane];
 }
 
 // Pre-subdivision kernels: one wave per NF fibers. The nodes to decide sit on
@@ -811,9 +813,9 @@ int fiber_validate(const float *fibers, int64_t fiber_stride, int64_t n_fibers, 
     if (!fibers || !mask_out) return FI_ERR_NULL;
     (void)hipGetLastError();
     // the excesses themselves need every search, the mask alone few
+    const int own = excess_out ? kBlock / 2 : kBlock;
     hipLaunchKernelGGL(excess_out ? k_validate<true> : k_validate<false>,
-                       dim3((unsigned)((n_fibers + kBlock - 1) / kBlock)), dim3(kBlock), 0, (hipStream_t)stream, fibers,
-                       fiber_stride, n_fibers, mask_out, excess_out);
+                       dim3((unsigned)((n_fibers + own - 1) / own)), dim3(kBlock), 0, (hipStream_t)stream, fibers, fiber_stride, n_fibers, mask_out, excess_out);
     return hipGetLastError() == hipSuccess ? FI_OK : FI_ERR_HIP;
 }
 
