@@ -285,7 +285,7 @@ struct Args {
 };
 
 // ---------------------------------------------------------------------------
-// FP64 surface solve inside a leaf (FI_FP64_REFINE)
+// FP64 surface solve (FI_FP64_REFINE)
 // ---------------------------------------------------------------------------
 //
 // The leaf cylinders converge to the solid swept by a disc of radius r(u)
@@ -293,19 +293,18 @@ struct Args {
 // of the cylinders maps the intersection to the closest point on the curve),
 // closed by the end discs. With refinement, a pair of depth > 16 runs the
 // traversal with every pruning test enlarged by a bound on its FP32 rounding,
-// so that no leaf holding part of that solid along the ray is pruned, and each
-// leaf the search reaches is checked in FP64: the first point of the solid
-// along the ray whose disc parameter u lies in the leaf's interval. A leaf
-// with no such point counts as missed and the search goes on; leaves are
-// reached front to back, so the first leaf that holds the solid gives the hit.
-// In the ray frame (ray point P = (0, 0, t)):
+// so that no leaf holding part of that solid along the ray is pruned. A pair
+// that reaches no leaf misses; one that does is decided in FP64 over the whole
+// curve. In the ray frame (ray point P = (0, 0, t)):
 //   the ray meets the disc plane of u at   t(u) = <C, C'> / C'_z
 //   it lies in that disc when              phi(u) = |P(t(u)) - C(u)|^2 - r(u)^2 <= 0
 //   boundary points solve                  f1 = <P - C, C'> = 0, f2 = |P - C|^2 - r^2 = 0
-// Candidates: Newton's method on (f1, f2) from the FP32 leaf hit; roots of
-// phi on the leaf interval (sampled, bracketed, then polished by Newton);
-// the end discs when the leaf touches u = 0 or 1; t = 0 when the origin lies
-// in one of the leaf's discs. The smallest candidate in [0, tmax) is the hit.
+// narrow_curve cuts the curve to the part within its radius of the ray (most
+// misses end there), simple_candidates decides short pieces with one closest
+// point, and curve_candidates searches the rest: Newton's method on (f1, f2)
+// from the FP32 leaf hit, roots of phi (sampled and bracketed), the end discs,
+// t = 0 when the origin lies in a disc. The smallest candidate in [0, tmax) is
+// the hit.
 
 constexpr int kRefineAbove = 16;         // refine pairs of depth > 16
 constexpr double kNewtonTol = 1e-9;      // relative residuals of an accepted Newton point
@@ -314,6 +313,7 @@ constexpr int kCurveSamples = 64;        // phi samples over the whole curve (lo
 struct Curve64 {
     double q[4][4];                      // control points in the FP64 ray frame (x, y, z, r)
     double scale;                        // largest control-point coordinate
+    bool regular;                        // the edges of the control polygon agree in direction (C' keeps away from 0)
 };
 
 // quad: F is a quadratic table (12 rows), taken as its exact cubic elevation
@@ -365,6 +365,14 @@ __device__ __forceinline__ bool curve_in_ray_frame(const float *R, int64_t rs, c
 #pragma unroll
     for (int k = 0; k < 4; ++k)
         c.scale = fmax(c.scale, fmax(fabs(c.q[k][0]), fmax(fabs(c.q[k][1]), fabs(c.q[k][2]))));
+    double e[3][3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int j = 0; j < 3; ++j) e[k][j] = c.q[k + 1][j] - c.q[k][j];
+    c.regular = e[0][0] * e[1][0] + e[0][1] * e[1][1] + e[0][2] * e[1][2] > 0.0 &&
+                e[1][0] * e[2][0] + e[1][1] * e[2][1] + e[1][2] * e[2][2] > 0.0 &&
+                e[0][0] * e[2][0] + e[0][1] * e[2][1] + e[0][2] * e[2][2] > 0.0;
     return true;
 }
 
@@ -506,7 +514,9 @@ __device__ __forceinline__ bool newton_surface(const Curve64 &c, double &t, doub
         t += dt;
         u += du;
         if (!(fabs(u) < 4.0) || !isfinite(t)) return false;
-        if (fabs(du) <= 4e-16 && fabs(dt) <= 4e-16 * fabs(t)) break;
+        // (next to a cusp the steps are left to go on: where they end decides)
+        const double eps = c.regular ? 1e-15 : 4e-16;
+        if (fabs(du) <= eps && fabs(dt) <= eps * fabs(t)) break;
     }
     double C[4], D[4], E[3];
     eval_curve(c, u, C, D, E);
@@ -521,8 +531,52 @@ __device__ __forceinline__ bool newton_surface(const Curve64 &c, double &t, doub
     return has_disc(c, D) && fabs(f2) <= kNewtonTol * scale && fabs(f1) <= kNewtonTol * C[3] * dn;
 }
 
-// Narrow a sign change of phi on [lo, hi] (lo_in: phi(lo) <= 0) to a
-// bracket of at most 2^-53, then polish the root by Newton's method, kept
+// The root of g = s z^2 + a^2 (s = C_x^2 + C_y^2 - r^2, a = C_x D_x + C_y D_y,
+// z = D_z: phi z^2, without a division) in a sign change [lo, hi] on which z
+// keeps its sign (lo_in: g(lo) <= 0), from the estimate x: Newton's method kept
+// inside the bracket, which every point narrows; a step that leaves it, or that
+// hardly shrinks, bisects. Ends at steps below 2^-53. Returns the
+// boundary point in (t, u).
+__device__ __forceinline__ void side_root(const Curve64 &c, double lo, double hi, bool lo_in, double x, double &t,
+                                          double &u)
+{
+    double last = hi - lo;
+    if (!(x > lo && x < hi)) x = 0.5 * (lo + hi);
+    for (int j = 0; j < 100; ++j) {
+        double C[4], D[4], E[3];
+        eval_curve(c, x, C, D, E);
+        const double a = C[0] * D[0] + C[1] * D[1];
+        const double s = C[0] * C[0] + C[1] * C[1] - C[3] * C[3];
+        const double da = 3.0 * (D[0] * D[0] + D[1] * D[1]) + 2.0 * (C[0] * E[0] + C[1] * E[1]);
+        const double z2 = D[2] * D[2];
+        const double g = fma(s, z2, a * a);
+        const double dg = fma(6.0 * (a - C[3] * D[3]), z2, fma(4.0 * s * D[2], E[2], 2.0 * a * da));
+        if ((g <= 0.0) == lo_in) lo = x;
+        else hi = x;
+        const double step = g / dg;
+        double y = x - step;
+        if (!(y > lo && y < hi) || !(fabs(step) <= 0.8 * last)) {
+            if (fabs(step) <= 0x1p-54) break;
+            y = 0.5 * (lo + hi);
+            if (!(y > lo && y < hi)) break;
+        }
+        last = fabs(y - x);
+        x = y;
+        if (last <= 0x1p-53) break;
+    }
+    u = x;
+    double C[4], D[4], E[3];
+    eval_curve(c, u, C, D, E);
+    t = circle_t(C, D, (C[0] * D[0] + C[1] * D[1] + C[2] * D[2]) / D[2]);
+}
+
+// The boundary point in a sign change of phi on [lo, hi] (lo_in:
+// phi(lo) <= 0): by side_root where the curve turns and slows down little on
+// the bracket and D_z keeps its size (to a factor of 4, by the Bernstein
+// coefficients of D), so that there is one. Otherwise (next to a cusp above
+// all) phi may have poles and more roots than one there, and the bracket is
+// narrowed step by step to
+// at most 2^-53, then the root polished by Newton's method, kept
 // only if it stays within a few final brackets (a polish that wanders
 // further follows the residual's rounding, not the root); returns the
 // boundary point in (t, u).
@@ -538,6 +592,31 @@ __device__ __forceinline__ bool newton_surface(const Curve64 &c, double &t, doub
 __device__ __forceinline__ bool boundary_root(const Curve64 &c, double lo, double hi, bool lo_in, double &t,
                                               double &u)
 {
+    if (c.regular) {
+        double C[4], D[4], E[3], F[4], G[3];
+        eval_curve(c, lo, C, D, E);
+        const double al = C[0] * D[0] + C[1] * D[1], sl = C[0] * C[0] + C[1] * C[1] - C[3] * C[3];
+        eval_curve(c, hi, C, F, G);
+        const double ah = C[0] * F[0] + C[1] * F[1], sh = C[0] * C[0] + C[1] * C[1] - C[3] * C[3];
+        const double mx = fma(hi - lo, E[0], D[0]), my = fma(hi - lo, E[1], D[1]), mz = fma(hi - lo, E[2], D[2]);
+        const double zs = copysign(1.0, D[2]) * fmin(fabs(D[2]), fmin(fabs(mz), fabs(F[2])));
+        const double zl = fmax(fabs(D[2]), fmax(fabs(mz), fabs(F[2])));
+        // of the three coefficients of D: least product with any other
+        const double dm = fmin(D[0] * mx + D[1] * my + D[2] * mz,
+                               fmin(F[0] * mx + F[1] * my + F[2] * mz, F[0] * D[0] + F[1] * D[1] + F[2] * D[2]));
+        const double dl = fmax(D[0] * D[0] + D[1] * D[1] + D[2] * D[2],
+                               fmax(mx * mx + my * my + mz * mz, F[0] * F[0] + F[1] * F[1] + F[2] * F[2]));
+        if (D[2] * F[2] > 0.0 && D[2] * mz > 0.0 && fabs(zs) >= 0.25 * zl && dm >= 0.25 * dl) {
+            const double gl = fma(sl, D[2] * D[2], al * al), gh = fma(sh, F[2] * F[2], ah * ah);
+            if ((gl <= 0.0) == lo_in && (gh <= 0.0) != lo_in) {
+                // the root of the parabola with its minimum at the inner end
+                const double gi = lo_in ? gl : gh, go = lo_in ? gh : gl, w = (hi - lo) * sqrt(gi / (gi - go));
+                side_root(c, lo, hi, lo_in, lo_in ? lo + w : hi - w, t, u);
+                eval_curve(c, u, C, D, E);
+                return has_disc(c, D);
+            }
+        }
+    }
     constexpr double kEps = 0x1p-54;                // half the final bracket
     // g = phi with the sign that makes g(lo) <= 0 <= g(hi). It only places
     // the estimate (the bracket follows the sign of phi, as in bisection),
@@ -618,58 +697,238 @@ __device__ __forceinline__ void bracket_polish(const Curve64 &c, double &t, doub
     }
 }
 
-// Boundary points of the swept solid along the ray with u in [ua, ub]; the
-// earliest with t in [tlo, thi] (the part of the ray the leaf owns) and below
-// tmax is kept in (t_best, u_best). (t0, u0) is the FP32 leaf hit. Also the
-// end discs when the interval reaches u = 0 or 1, and t = 0 when the origin
-// lies in one of the discs. The earliest boundary point of the solid is its
-// entry (or the origin, when inside), so no entry/exit classification is
-// needed.
-// The search runs in two passes so that the lanes of a wave stay together:
-// the first samples phi at the NS + 1 parameters and records, per sample
-// interval, the events that need a search (a sign change of phi, a local
-// minimum of phi above zero, a crossing of the disc plane through the origin)
-// as bit masks; the second searches the recorded events one after another.
-// A wave then runs one search per event of its busiest lane, not the union
-// of every lane's searches at every sample.
-template <int NS>
-__device__ __forceinline__ void leaf_candidates(const Curve64 &c, double ua, double ub, double tlo, double thi,
-                                                double tmax, double t0, double u0, double &t_best,
-                                                double &u_best)
+// The part [a, b] of the curve outside which it stays further than its
+// radius from the ray: every boundary point, end disc and disc that holds the
+// origin lies at |C_xy(u)| <= r(u). The piece on [a, b] stays within
+// 3/4 max |e_k| of its chord at the same parameter (e_k: what the inner
+// control points are off the chord's third points), so only parameters whose
+// chord point lies within that plus the largest radius of the ray remain: an
+// interval. Each round narrows the piece to it; what the piece bends off its
+// chord falls with the square of its length, so two to four rounds leave
+// little more than the part within the radius. False when nothing remains:
+// the ray misses. The hardware reciprocal and root (2^-22) are covered by the
+// 1e-5 added to the distance and the 1e-6 added to the interval.
+struct Part {
+    double a, b;
+    double reach;                        // the piece's distance bound from its chord, radius included
+};
+
+// One round on the piece [p.a, p.b]: 0 nothing remains, 1 narrowed to a piece
+// of at least 0.7 of it (or not at all), 2 narrowed further.
+__device__ __forceinline__ int narrow_piece(const Curve64 &c, Part &p)
 {
-    constexpr int kWords = (NS + 1 + 31) / 32;
+    const double w = p.b - p.a;
+    double p0[3], p3[3], d0[3], d3[3];              // x, y, r of the piece: ends and end edges
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const double u = e ? p.b : p.a, v = 1.0 - u;
+        const double b0 = v * v * v, b1 = 3.0 * u * v * v, b2 = 3.0 * u * u * v, b3 = u * u * u;
+        const double e0 = v * v, e1 = 2.0 * u * v, e2 = u * u;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int j = k < 2 ? k : 3;
+            const double C = fma(b0, c.q[0][j], fma(b1, c.q[1][j], fma(b2, c.q[2][j], b3 * c.q[3][j])));
+            const double D = fma(e0, c.q[1][j] - c.q[0][j],
+                                 fma(e1, c.q[2][j] - c.q[1][j], e2 * (c.q[3][j] - c.q[2][j]))) * w;
+            (e ? p3 : p0)[k] = C;
+            (e ? d3 : d0)[k] = D;
+        }
+    }
+    const double dx = p3[0] - p0[0], dy = p3[1] - p0[1];
+    constexpr double third = 1.0 / 3.0;
+    const double ax = fma(-third, dx, d0[0]), ay = fma(-third, dy, d0[1]);
+    const double bx = fma(-third, dx, d3[0]), by = fma(-third, dy, d3[1]);
+    const double bend = fmax(fma(ax, ax, ay * ay), fma(bx, bx, by * by));
+    const double rad = fmax(fmax(fabs(p0[2]), fabs(p3[2])), fmax(fabs(p0[2] + d0[2]), fabs(p3[2] - d3[2])));
+    p.reach = fma(0.75 * 1.00001, bend > 0.0 ? bend * __builtin_amdgcn_rsq(bend) : 0.0,
+                  fma(1.00001, rad, 1e-14 * c.scale));
+    const double dd = fma(dx, dx, dy * dy);
+    const double inv = __builtin_amdgcn_rcp(dd);
+    const double cr = p0[0] * dy - p0[1] * dx;
+    const double rest = fma(p.reach, p.reach, -(cr * cr) * inv * (1.0 - 1e-6));
+    if (rest < 0.0) return 0;
+    const double half = rest * inv;
+    if (!(half > 0.0 && half < 1e30)) return 1;     // no chord across the ray: nothing to narrow by
+    const double h = half * __builtin_amdgcn_rsq(half) * (1.0 + 1e-6);
+    const double mid = -fma(p0[0], dx, p0[1] * dy) * inv;
+    const double pad = fma(1e-6, fabs(mid) + h, 1e-6);
+    const double lo = mid - h - pad, hi = mid + h + pad;
+    if (hi < 0.0 || lo > 1.0) return 0;
+    p.b = hi < 1.0 ? fma(w, hi, p.a) : p.b;
+    p.a = lo > 0.0 ? fma(w, lo, p.a) : p.a;
+    return p.b - p.a < 0.7 * w ? 2 : 1;
+}
+
+__device__ __forceinline__ bool narrow_curve(const Curve64 &c, Part &p)
+{
+    p.a = 0.0;
+    p.b = 1.0;
+    int r = 2;
+    for (int it = 0; it < 5 && r == 2; ++it) r = narrow_piece(c, p);
+    return r != 0;
+}
+
+// Boundary points of a piece on which the curve is nearly straight, the part
+// that can lie within its radius of the ray being short (on hair a few
+// thousandths of the curve). With s = C_x^2 + C_y^2 - r^2,
+// a = C_x D_x + C_y D_y and z = D_z, phi = s + (a / z)^2: where the curve is
+// closest to the ray (a = 0, at xn) phi is s, and phi is close to the
+// parabola s - 6 r D_r (u - xn) + K (u - xn)^2, K = (a' / z)^2 + 3 a'. So one
+// evaluation decides whether the ray meets the side, and Newton's method on
+// g = s z^2 + a^2 finds both boundary points from the parabola's roots in two
+// or three steps, for grazing rays too. False where the piece is not that
+// simple -- it bends, the discs are nearly parallel to the ray, the taper is
+// steep, the ray touches within the taper's or the residual test's reach, the
+// origin lies between the boundary points -- and the search below decides.
+__device__ __forceinline__ bool simple_candidates(const Curve64 &c, const Part &part, double tmax, double &t_best,
+                                                  double &u_best)
+{
+    const double lo = part.a, hi = part.b, v = hi - lo;
+    if (!(v <= 0.5)) return false;
+    double al, ah;
+    {
+        // phi has one minimum on the piece: a grows (a' = 3 D_xy^2 + 2 <C, E>_xy,
+        // |C_xy| within the reach), z keeps its sign, and a / z grows with a
+        // (|a z'| < a' |z|, z' = 2 E_z), so that s and (a / z)^2 both fall
+        // before the closest point and rise after it; a mild taper moves the
+        // minimum a little. Bounds from the Bernstein coefficients of D
+        // (three) and E (its ends).
+        double C[4], D[4], E[3], F[4], G[3];
+        eval_curve(c, lo, C, D, E);
+        al = C[0] * D[0] + C[1] * D[1];
+        eval_curve(c, hi, C, F, G);
+        ah = C[0] * F[0] + C[1] * F[1];
+        const double ex = fmax(fabs(E[0]), fabs(G[0])), ey = fmax(fabs(E[1]), fabs(G[1]));
+        const double ez = fmax(fabs(E[2]), fabs(G[2])), e2 = fma(ex, ex, ey * ey);
+        const double mx = fma(v, E[0], D[0]), my = fma(v, E[1], D[1]), mz = fma(v, E[2], D[2]);
+        const double sx = D[0] + F[0], sy = D[1] + F[1];
+        const double low = fmin(fma(D[0], sx, D[1] * sy), fmin(fma(mx, sx, my * sy), fma(F[0], sx, F[1] * sy)));
+        if (!(low > 0.0)) return false;
+        const double dmin = low * low * __builtin_amdgcn_rcp(fma(sx, sx, sy * sy)) * 0.999999;
+        const double dmax = fmax(fma(D[0], D[0], D[1] * D[1]), fmax(fma(mx, mx, my * my), fma(F[0], F[0], F[1] * F[1])));
+        const double sg = copysign(1.0, D[2]), z = fmin(sg * D[2], fmin(sg * mz, sg * F[2]));
+        const double R = part.reach;
+        if (!(z > 0.0) || !(z * z >= 0x1p-20 * (dmax + z * z)) || !(4.0 * R * R * e2 <= dmin * dmin) ||
+            !(16.0 * R * R * dmax * ez * ez <= dmin * dmin * z * z))
+            return false;
+        const double er = fmax(fabs(c.q[2][3] - 2.0 * c.q[1][3] + c.q[0][3]), fabs(c.q[3][3] - 2.0 * c.q[2][3] + c.q[1][3]));
+        const double dr = fma(v, er, fmax(fabs(D[3]), fabs(F[3])));
+        if (!(16.0 * dr * dr <= dmin) || !(8.0 * R * er <= dmin)) return false;
+    }
+    // ends of the piece: outside but where the curve itself ends
+    double t, phi = 1.0, ts = INFINITY, us = 0.0;
+    const bool lo_in = lo <= 0.0 && disc_point(c, 0.0, t, phi) && phi <= 0.0;
+    if (lo_in) { ts = t; us = 0.0; }
+    const bool hi_in = hi >= 1.0 && disc_point(c, 1.0, t, phi) && phi <= 0.0;
+    if (hi_in && t < ts) { ts = t; us = 1.0; }
+    if (ts <= 0.0) return false;
+    // closest point: Newton's method inside the bracket
+    double xn = al >= 0.0 ? lo : hi, C[4], D[4], E[3];
+    if (al < 0.0 && ah > 0.0) {
+        double l = lo, h = hi, last = v;
+        xn = fma(v, al / (al - ah), lo);
+        for (int j = 0; j < 60; ++j) {
+            eval_curve(c, xn, C, D, E);
+            const double a = C[0] * D[0] + C[1] * D[1];
+            const double da = 3.0 * (D[0] * D[0] + D[1] * D[1]) + 2.0 * (C[0] * E[0] + C[1] * E[1]);
+            if (a > 0.0) h = xn;
+            else l = xn;
+            const double step = a / da;
+            double y = xn - step;
+            if (!(y > l && y < h) || !(fabs(step) <= 0.8 * last)) {
+                if (fabs(step) <= 0x1p-54) break;
+                y = 0.5 * (l + h);
+                if (!(y > l && y < h)) break;
+            }
+            last = fabs(y - xn);
+            xn = y;
+            if (last <= 0x1p-40) break;          // phi is flat there: enough to decide by
+        }
+    }
+    eval_curve(c, xn, C, D, E);
+    const double r2 = C[3] * C[3], s = C[0] * C[0] + C[1] * C[1] - r2;
+    const double da = 3.0 * (D[0] * D[0] + D[1] * D[1]) + 2.0 * (C[0] * E[0] + C[1] * E[1]);
+    const double K = fma(da / D[2], da / D[2], 3.0 * da), rd = 3.0 * C[3] * D[3];
+    const bool inner = xn > lo && xn < hi;
+    const double room = 4.0 * (rd * rd / K) + 4.0 * kNewtonTol * r2;
+    if (fabs(s) <= room) return false;                          // touches
+    if (!inner && !(lo_in || hi_in)) {
+        // the closest point is an end of the curve: outside its disc, the
+        // side is not met unless the taper or the discs' tilt reaches back
+        const double a = C[0] * D[0] + C[1] * D[1];
+        const double f = s + (a / D[2]) * (a / D[2]);
+        if (!(f > 0.0) || !(s > 0.0)) return false;
+        const double f1 = 6.0 * (a - C[3] * D[3]) + 2.0 * (a / D[2]) * (da / D[2]);
+        if ((xn == lo) != (f1 > 0.0)) return false;             // phi falls into the piece
+    }
+    if (ts < tmax && ts < t_best) { t_best = ts; u_best = us; }
+    const bool n_in = inner ? s < 0.0 : xn == lo ? lo_in : hi_in;
+    const double w = sqrt(fmax(-s, 0.0) / K);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const double l = j ? xn : lo, h = j ? hi : xn;
+        const bool li = j ? n_in : lo_in, hin = j ? hi_in : n_in;
+        if (li == hin || !(h > l)) continue;
+        if (!inner && s > 0.0) return false;
+        double tr, ur;
+        side_root(c, l, h, li, j ? xn + w : xn - w, tr, ur);
+        if (!(tr > 0.0)) return false;                          // the origin may be inside
+        if (tr < tmax && tr < t_best) { t_best = tr; u_best = ur; }
+    }
+    return true;
+}
+
+// Boundary points of the swept solid along the ray; the earliest with t in
+// [0, tmax) is kept in (t_best, u_best). (t0, u0) is the FP32 leaf hit. Also the
+// end discs, and t = 0 when the origin lies in one of the discs. The earliest
+// boundary point of the solid is its entry (or the origin, when inside), so
+// no entry/exit classification is needed.
+// For the pairs that narrow_curve and simple_candidates leave open. phi is
+// sampled at the parameters k / kCurveSamples about the part of the curve that
+// can lie within its radius of the ray (elsewhere phi is above zero and
+// nothing can be found) in two passes, so that the lanes of a wave stay
+// together: the first records, per sample interval, the events that need a
+// search (a sign change of phi, a local minimum of phi above zero, a crossing
+// of the disc plane through the origin) as bit masks; the second searches the
+// recorded events one after another. A wave then runs one search per event of
+// its busiest lane, not the union of every lane's searches at every sample.
+__device__ __forceinline__ void curve_candidates(const Curve64 &c, const Part &part, double tmax, double t0, double u0,
+                                                 double &t_best, double &u_best)
+{
+    constexpr int NS = kCurveSamples;
     auto take = [&](double t, double u) {
-        if (t >= tlo && t <= thi && t < tmax && t < t_best) { t_best = t; u_best = u; }
+        if (t >= 0.0 && t < tmax && t < t_best) { t_best = t; u_best = u; }
     };
     {
         double t = t0, u = u0;
         if (newton_surface(c, t, u)) {
             bracket_polish(c, t, u);
-            if (u >= ua && u <= ub) take(t, u);
+            if (u >= 0.0 && u <= 1.0) take(t, u);
         }
     }
-    const double h = (ub - ua) / NS;
-    auto at = [&](int k) { return k == NS ? ub : ua + h * k; };
-    // sample k (0..NS): inside (phi <= 0) and t <= 0 flags; events on (k-1, k]
-    uint32_t in_m[kWords], tneg_m[kWords], sign_m[kWords], min_m[kWords], org_m[kWords];
-#pragma unroll
-    for (int q = 0; q < kWords; ++q) in_m[q] = tneg_m[q] = sign_m[q] = min_m[q] = org_m[q] = 0u;
+    auto at = [](int k) { return (double)k * (1.0 / NS); };
+    // every event whose search could find a point has its bracket, up to two
+    // sample intervals, about the part: samples k0..k1
+    const int k0 = max(0, (int)floor(part.a * NS) - 2), k1 = min(NS, (int)ceil(part.b * NS) + 2);
+    // sample k (k < 64): inside (phi <= 0) and t <= 0 flags in bit k; events
+    // on (k-1, k] in bit k-1
+    uint64_t in_m = 0, tneg_m = 0, sign_m = 0, min_m = 0, org_m = 0;
     // the first sample counts as a minimum (event 1) only where phi turns
     // inside the first interval
-    double pt = 0.0, pphi = 0.0, ppphi = ua == 0.0 && !end_turns(c, 0.0) ? -INFINITY : INFINITY;
-    bool pok = disc_point(c, ua, pt, pphi);
-    if (pok && pphi <= 0.0) in_m[0] |= 1u;
-    if (pok && pt <= 0.0) tneg_m[0] |= 1u;
-    for (int k = 1; k <= NS; ++k) {
+    double pt = 0.0, pphi = 0.0, ppphi = k0 > 0 || !end_turns(c, 0.0) ? -INFINITY : INFINITY;
+    bool pok = disc_point(c, at(k0), pt, pphi);
+    if (pok && pphi <= 0.0) in_m |= (uint64_t)1 << k0;
+    if (pok && pt <= 0.0) tneg_m |= (uint64_t)1 << k0;
+    for (int k = k0 + 1; k <= k1; ++k) {
         double ct = 0.0, cphi = 0.0;
         const bool cok = disc_point(c, at(k), ct, cphi);
-        const uint32_t bit = 1u << (k & 31);
-        if (cok && cphi <= 0.0) in_m[k >> 5] |= bit;
-        if (cok && ct <= 0.0) tneg_m[k >> 5] |= bit;
+        const uint64_t bit = (uint64_t)1 << (k - 1);
+        if (cok && cphi <= 0.0 && k < NS) in_m |= bit << 1;
+        if (cok && ct <= 0.0 && k < NS) tneg_m |= bit << 1;
         if (pok && cok) {
-            if ((pphi <= 0.0) != (cphi <= 0.0)) sign_m[k >> 5] |= bit;
-            else if (pphi > 0.0 && cphi > pphi && ppphi > pphi) min_m[k >> 5] |= bit;
-            if ((pt <= 0.0) != (ct <= 0.0) && (pphi <= 0.0 || cphi <= 0.0) && tlo <= 0.0) org_m[k >> 5] |= bit;
+            if ((pphi <= 0.0) != (cphi <= 0.0)) sign_m |= bit;
+            else if (pphi > 0.0 && cphi > pphi && ppphi > pphi) min_m |= bit;
+            if ((pt <= 0.0) != (ct <= 0.0) && (pphi <= 0.0 || cphi <= 0.0)) org_m |= bit;
         }
         ppphi = pok ? pphi : INFINITY;
         pt = ct; pphi = cphi; pok = cok;
@@ -678,23 +937,11 @@ __device__ __forceinline__ void leaf_candidates(const Curve64 &c, double ua, dou
     // two samples (as at a stalled end, where the disc planes turn fast as
     // u -> 1), where phi turns before the end; recorded as the event of a
     // minimum at sample NS - 1 (searched on (u[NS-2], u[NS]), which holds it)
-    if (pok && pphi > 0.0 && ppphi > pphi && (ub < 1.0 || end_turns(c, 1.0)))
-        min_m[NS >> 5] |= 1u << (NS & 31);
-    // masks are indexed with unrolled selects (no dynamic register indexing)
-    auto flag = [&](const uint32_t *m, int k) {
-        uint32_t w = 0u;
-#pragma unroll
-        for (int q = 0; q < kWords; ++q) w = q == (k >> 5) ? m[q] : w;
-        return ((w >> (k & 31)) & 1u) != 0u;
-    };
-    auto next_event = [&](uint32_t *m) {       // lowest recorded event, removed from the mask
-        int k = -1;
-#pragma unroll
-        for (int q = kWords - 1; q >= 0; --q)
-            if (m[q]) k = 32 * q + __builtin_ctz(m[q]);
-#pragma unroll
-        for (int q = 0; q < kWords; ++q)
-            if (k >= 0 && q == (k >> 5)) m[q] &= m[q] - 1u;
+    if (k1 == NS && pok && pphi > 0.0 && ppphi > pphi && end_turns(c, 1.0)) min_m |= (uint64_t)1 << (NS - 1);
+    auto flag = [](uint64_t m, int k) { return ((m >> k) & 1u) != 0u; };
+    auto next_event = [](uint64_t &m) {        // lowest recorded event (1..NS; -1: none), removed from the mask
+        const int k = m ? __builtin_ctzll(m) + 1 : -1;
+        m &= m - 1u;
         return k;
     };
     // sign changes: one boundary point between the samples
@@ -717,6 +964,9 @@ __device__ __forceinline__ void leaf_candidates(const Curve64 &c, double ua, dou
         {
             constexpr double g = 0.38196601125010515;         // golden-section step
             double a = at(k >= 2 ? k - 2 : 0), b = at(k), tt;
+            // phi stays above zero where the curve stays off the ray
+            Part dip{a, b, 0.0};
+            if (narrow_piece(c, dip) == 0) continue;
             const double tol = (b - a) * 0x1p-35;
             double x = at(k - 1), fx = 0.0;
             bool ok = disc_point(c, x, tt, fx);
@@ -798,7 +1048,7 @@ __device__ __forceinline__ void leaf_candidates(const Curve64 &c, double ua, dou
     // end discs
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        if ((e == 0 && ua > 0.0) || (e == 1 && ub < 1.0)) continue;
+        if ((e == 0 && part.a > 0.0) || (e == 1 && part.b < 1.0)) continue;
         double C[4], D[4], E[3];
         eval_curve(c, (double)e, C, D, E);
         end_disc_normal(c, (double)e, D);      // a vanishing end tangent: the limit plane
@@ -911,16 +1161,9 @@ __device__ __forceinline__ float leaf_u(const Lane &L)
     return fmaf(ul, (float)L.size * 0x1p-23f, (float)(L.start & kStartMask) * 0x1p-23f);
 }
 
-// FP64 decision of a pair of depth > 16 once the conservative search reaches
-// its first leaf: the earliest boundary point of the swept solid along the
-// ray over the whole curve, t in [0, tmax), from kCurveSamples samples of the
-// disc excess (with the FP32 leaf hit as Newton's start). A leaf-local check
-// (three leaves around the FP32 hit, then the whole curve if it failed) was
-// measured first: at hair scale almost every leaf check failed (the FP32
-// leaf lies more than a leaf from the entry), so it only added work.
-// Arguments and result go by value: a reference to the caller's lane state
-// or to the kernel's arguments would keep them in scratch memory for the
-// whole kernel (the call is not inlined), every trip included.
+// FP64 decision of a pair of depth > 16 whose conservative search reached a
+// leaf: the earliest boundary point of the swept solid along the ray over the
+// whole curve, t in [0, tmax).
 struct Refined {
     double t = INFINITY, u = __builtin_nan("");
     bool hit = false;
@@ -962,21 +1205,11 @@ __device__ __forceinline__ void solid_normal(const Curve64 &c, double t, double 
     n[2] = ez + tilt * D[2] / dl;
 }
 
-// `fiber` >= 0 names the fiber directly (candidate lists); `tmax` is the
-// FP64 limit of the search.
-__device__ __noinline__ Refined refine_whole_curve(const float *rays, int64_t ray_stride, const float *fibers,
-                                                   int64_t fiber_stride, const int32_t *pair_ray,
-                                                   const int32_t *pair_fiber, int64_t i, int64_t fiber,
-                                                   double tmax, float t0, float u0, bool normal, bool quad)
+// The result of a search that ended at (t, u), with the normal turned back
+// into world space.
+__device__ __forceinline__ Refined refined_at(const Curve64 &cv, const double frame[9], double t, double u, bool normal)
 {
     Refined r;
-    const int64_t ri = pair_ray ? (int64_t)pair_ray[i] : i;
-    const int64_t fi = fiber >= 0 ? fiber : pair_fiber ? (int64_t)pair_fiber[i] : i;
-    Curve64 cv;
-    double frame[9];
-    if (!curve_in_ray_frame(rays + ri, ray_stride, fibers + fi, fiber_stride, cv, frame, quad)) return r;
-    double t = INFINITY, u = __builtin_nan("");
-    leaf_candidates<kCurveSamples>(cv, 0.0, 1.0, 0.0, tmax, tmax, (double)t0, (double)u0, t, u);
     if (t < INFINITY) {
         r.t = t;
         r.u = u;
@@ -995,6 +1228,28 @@ __device__ __noinline__ Refined refine_whole_curve(const float *rays, int64_t ra
         }
     }
     return r;
+}
+
+// Candidate lists: the decision inside the traversal kernel, for fiber `fi`
+// within `tmax`, the ray shortened to its FP64 nearest hit so far. Arguments
+// and result go by value: a reference to the caller's lane state or to the
+// kernel's arguments would keep them in scratch memory for the whole kernel
+// (the call is not inlined), every trip included.
+__device__ __noinline__ Refined refine_whole_curve(const float *rays, int64_t ray_stride, const float *fibers,
+                                                   int64_t fiber_stride, int64_t ri, int64_t fi, double tmax, float t0,
+                                                   float u0, bool normal)
+{
+    Curve64 cv;
+    double frame[9];
+    if (!curve_in_ray_frame(rays + ri, ray_stride, fibers + fi, fiber_stride, cv, frame, false)) return Refined{};
+    double t = INFINITY, u = __builtin_nan("");
+    Part part;
+    if (narrow_curve(cv, part) && !simple_candidates(cv, part, tmax, t, u)) {
+        t = INFINITY;
+        u = __builtin_nan("");
+        curve_candidates(cv, part, tmax, (double)t0, (double)u0, t, u);
+    }
+    return refined_at(cv, frame, t, u, normal);
 }
 
 // One loop trip of the paper's iteration (Appendix C, final listing): a
@@ -1149,14 +1404,15 @@ __device__ __forceinline__ bool stalled_end(const Lane &L)
     return end && e <= rel && e <= stall_abs(L.root);
 }
 
-// PC: the parent cache in LDS (else every backtrack replays from the root)
-template <int MODE, bool QUAD, bool PC, class Root>
+// PC: the parent cache in LDS (else every backtrack replays from the root).
+// PARK: a refined pair's lane parks at its first leaf (candidate lists).
+template <int MODE, bool QUAD, bool PC, bool PARK, class Root>
 __device__ __forceinline__ int trip(Lane &L, const Root &root, float *col, HitGeo &hg)
 {
     float te, tx, lo, hi;
     bool vis = node_visible<MODE, QUAD>(L.c, L.lo, L.hi, L.slack, te, tx, lo, hi);
     const bool leaf = L.size <= L.min_size || stalled_end(L);
-    if (MODE == kConservative && vis && leaf && L.slack >= 0.0f) {
+    if (MODE == kConservative && PARK && vis && leaf && L.slack >= 0.0f) {
         // refinement: the first leaf reached means the solid may be hit; park
         // the lane (empty interval, no pending sibling) until the wave decides
         // its parked pairs in FP64, keeping the leaf hit as Newton's start
@@ -1292,7 +1548,10 @@ __device__ __forceinline__ void leaf_normal(const Args &a, int64_t i, const Lane
 // onto the leaf chord; hit when t < tmax). A refined pair (depth > 16 under
 // FI_FP64_REFINE) reports its FP64 surface hit, decided in FP64.
 // `hg` is the leaf geometry of a plain hit; `ref` the FP64 result of a
-// refined pair (used when `reached`). CAND: candidate lists (see Args).
+// refined candidate (used when `reached`). A refined pair that reached a leaf
+// is marked for refine_range instead, its FP32 leaf hit in t and u. CAND:
+// candidate lists (see Args).
+constexpr uint8_t kToRefine = 2;               // hit_out of a pair that refine_range decides
 template <int MODE, bool CAND = false>
 __device__ __forceinline__ void finish(const Args &a, int64_t i, const Lane &L, bool reached,
                                        HitGeo hg = HitGeo{}, Refined ref = Refined{})
@@ -1300,8 +1559,14 @@ __device__ __forceinline__ void finish(const Args &a, int64_t i, const Lane &L, 
     float t = INFINITY, u = __builtin_nanf("");
     double t64 = INFINITY, u64 = __builtin_nan("");
     bool hit = false;
+    if (MODE == kConservative && !CAND && L.slack >= 0.0f && reached) {
+        a.t_out[i] = L.t;
+        a.u_out[i] = L.u;
+        a.hit_out[i] = kToRefine;
+        return;
+    }
     if (MODE == kConservative && L.slack >= 0.0f) {
-        if (reached) {
+        if (CAND && reached) {
             t64 = ref.t;
             u64 = ref.u;
             t = (float)t64;
@@ -1549,6 +1814,98 @@ __device__ __forceinline__ void wave_range(int64_t w, int64_t waves, int64_t cou
     end = (w + 1) * share < count ? (w + 1) * share : count;
 }
 
+// The FP64 decisions of a wave's pairs begin .. end - 1 that reached a leaf
+// (hit_out == kToRefine), once its traversal is done. The wave lists those
+// marked, up to kList pairs at a time, decides each with a lane of its own as
+// far as narrow_curve and simple_candidates go, lists what they leave open and
+// searches that, so that both passes run with full waves and no lane waits,
+// parked, for the last of its wave. Bound by FP64 arithmetic and, beside it, by
+// the longest pairs of the traversal, which the other waves' decisions hide: a
+// kernel of its own for the decisions was as fast on hair (409 against 399 us
+// per 10^6 pairs) but waited for them (500,009 degenerate pairs 1.57 against
+// 1.14 ms). Before, with the lanes parked at their leaves and every pair
+// running 65 samples and two long bracketed searches: 1.14 and 1.41 ms.
+constexpr int kList = 16 * kWave;              // pairs listed at a time
+
+template <bool BATCHED, bool QUAD>
+__device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes, const int64_t *offsets, int n_scenes,
+                                             int64_t begin, int64_t end, const float *aos, int *list, int *open)
+{
+    const int lane = (int)threadIdx.x;
+    int scene0 = 0;
+    if constexpr (BATCHED) scene0 = find_scene(offsets, n_scenes, begin);
+    for (int64_t first = begin; first < end; first += kList) {
+        const int size = end - first < kList ? (int)(end - first) : kList;
+        // pair k of this part: its index in its scene, and the scene
+        auto place = [&](int k, int &sc) {
+            int64_t i = first + k;
+            if constexpr (BATCHED) {
+                sc = scene0;
+                while (sc + 1 < n_scenes && offsets[sc + 1] <= i) ++sc;
+                i -= offsets[sc];
+            }
+            return i;
+        };
+        int n = 0, n_open = 0;
+        for (int k0 = 0; k0 < size; k0 += kWave) {
+            bool marked = false;
+            if (k0 + lane < size) {
+                int sc = 0;
+                const int64_t i = place(k0 + lane, sc);
+                marked = (BATCHED ? scenes[sc].hit_out : a0.hit_out)[i] == kToRefine;
+            }
+            const uint64_t m = __ballot(marked);
+            if (marked) list[n + (int)lanes_below(m)] = k0 + lane;
+            n += __popcll(m);
+        }
+        __syncthreads();
+        for (int pass = 0; pass < 2; ++pass) {
+            const int todo = pass ? n_open : n;
+            for (int e0 = 0; e0 < todo; e0 += kWave) {
+                bool left = false;
+                int k = 0;
+                if (e0 + lane < todo) {
+                    k = (pass ? open : list)[e0 + lane];
+                    int sc = 0;
+                    const int64_t i = place(k, sc);
+                    const Args &a = BATCHED ? scenes[sc] : a0;
+                    const int64_t ri = a.pair_ray ? (int64_t)a.pair_ray[i] : i;
+                    const int64_t fi = a.pair_fiber ? (int64_t)a.pair_fiber[i] : i;
+                    Curve64 cv;
+                    double frame[9];
+                    double t = INFINITY, u = __builtin_nan("");
+                    // (a marked pair has a finite, non-zero direction)
+                    curve_in_ray_frame(a.rays + ri, a.ray_stride, aos ? aos + 16 * fi : a.fibers + fi,
+                                       aos ? 1 : a.fiber_stride, cv, frame, QUAD);
+                    const double tmax = a.rays[6 * a.ray_stride + ri];
+                    Part part;
+                    if (narrow_curve(cv, part)) {
+                        if (pass) curve_candidates(cv, part, tmax, (double)a.t_out[i], (double)a.u_out[i], t, u);
+                        else left = !simple_candidates(cv, part, tmax, t, u);
+                    }
+                    if (!left) {
+                        const Refined r = refined_at(cv, frame, t, u, a.normal_out != nullptr);
+                        a.t_out[i] = (float)r.t;
+                        a.u_out[i] = (float)r.u;
+                        a.hit_out[i] = r.hit ? 1 : 0;
+                        a.t64_out[i] = r.t;
+                        a.u64_out[i] = r.u;
+                        if (a.normal_out) {
+                            a.normal_out[i] = r.nx;
+                            a.normal_out[a.n_pairs + i] = r.ny;
+                            a.normal_out[2 * a.n_pairs + i] = r.nz;
+                        }
+                    }
+                }
+                const uint64_t m = __ballot(left);
+                if (left) open[n_open + (int)lanes_below(m)] = k;
+                n_open += __popcll(m);
+            }
+            __syncthreads();
+        }
+    }
+}
+
 #ifndef FIBERHIT_WAVES
 #define FIBERHIT_WAVES 4                      // build knob: register budget (waves per SIMD)
 #endif
@@ -1559,6 +1916,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
 {
     __shared__ float s_cache[16 * kWave];
     __shared__ float s_queue[kQWords * kQueue];
+    static_assert(kQWords * kQueue >= kList && 16 * kWave >= kList, "refine_range lists its pairs there");
     const int lane = (int)threadIdx.x;
     float *col = s_cache + lane;
     const int64_t w = blockIdx.x, waves = gridDim.x;
@@ -1711,7 +2069,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         // of the call).
         if (__ballot(active) == 0 && next >= end && q_count == 0) break;
         HitGeo hg;
-        const int st = trip<MODE, QUAD, PC>(L, root, col, hg);
+        const int st = trip<MODE, QUAD, PC, CAND>(L, root, col, hg);
         if (active && st != kGoOn && !(MODE == kConservative && L.waiting)) {
             if constexpr (BATCHED) {
                 // lanes of the wave's current scene read its output
@@ -1724,7 +2082,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
             }
             active = false;
         }
-        if constexpr (MODE == kConservative) {
+        if constexpr (MODE == kConservative && CAND) {
             // the FP64 searches run for all parked lanes at once (SIMD lanes
             // of one call) when no busy lane is left: every lane of the wave
             // then shares the search's passes (measured: 2x faster on hair
@@ -1735,33 +2093,18 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                     L.waiting = 0;
                     // plain values, not references (see refine_whole_curve)
                     const float *rays = a0.rays, *fibers = a0.fibers;
-                    int64_t rs = a0.ray_stride, fs = a0.fiber_stride;
-                    const int32_t *pr = a0.pair_ray, *pf = a0.pair_fiber;
-                    bool want_n = a0.normal_out != nullptr;
-                    if constexpr (BATCHED) {
-                        const Args *sc = scenes + L.scene;
-                        rays = sc->rays; fibers = sc->fibers;
-                        rs = sc->ray_stride; fs = sc->fiber_stride;
-                        pr = sc->pair_ray; pf = sc->pair_fiber;
-                        want_n = sc->normal_out != nullptr;
-                    }
-                    int64_t fi = -1;
-                    double tlim = L.tmax;
-                    if (CAND) {
-                        // candidate lists: the ray's tmax shortened to its
-                        // FP64 nearest hit so far
-                        fi = a0.cand_fiber[a0.cand_off[L.pair] + a0.cand_round];
-                        tlim = fmin((double)rays[6 * rs + L.pair], a0.t64_out[L.pair]);
-                    }
-                    const int32_t pair = L.pair, scene = L.scene;
-                    const Refined r = refine_whole_curve(rays, rs, fibers, fs, pr, pf, pair, fi, tlim, L.t, L.ru,
-                                                         want_n, QUAD);
+                    const int64_t rs = a0.ray_stride, fs = a0.fiber_stride;
+                    // the ray's tmax shortened to its FP64 nearest hit so far
+                    const int64_t fi = a0.cand_fiber[a0.cand_off[L.pair] + a0.cand_round];
+                    const double tlim = fmin((double)rays[6 * rs + L.pair], a0.t64_out[L.pair]);
+                    const int32_t pair = L.pair;
+                    const Refined r = refine_whole_curve(rays, rs, fibers, fs, pair, fi, tlim, L.t, L.ru,
+                                                         a0.normal_out != nullptr);
                     // the output pointers are read after the call (not kept
                     // live across it); a refined pair's finish reads only the
                     // search's result from the lane (slack >= 0)
                     Lane R = {};
-                    if constexpr (BATCHED) finish<MODE>(scenes[scene], pair, R, r.hit, HitGeo{}, r);
-                    else finish<MODE, CAND>(a0, pair, R, r.hit, HitGeo{}, r);
+                    finish<MODE, CAND>(a0, pair, R, r.hit, HitGeo{}, r);
                     active = false;
                 }
                 // every lane is free now. Its traversal state is reset, so
@@ -1775,6 +2118,13 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
             L.hi = -INFINITY;
             L.bits = 0;
         }
+    }
+    if constexpr (MODE == kConservative && !CAND) {
+        // the wave's own marks, written above by other lanes
+        __threadfence_block();
+        __syncthreads();
+        wave_range(w, waves, count, next, end);
+        refine_range<BATCHED, QUAD>(a0, scenes, offsets, n_scenes, next, end, aos, (int *)s_cache, (int *)s_queue);
     }
 }
 
@@ -2036,18 +2386,23 @@ void remember_tuning(const fi_scene *sc, int32_t n, bool refine, const fi_tuning
 // the deep call's), a grid skewed towards the waves that start first on
 // each SIMD, and issue priority by progress through the share. The rounds
 // of candidate lists keep the resident waves: most of their pairs end at
-// the root, and twice the waves made them 15 % (refined 39 %) slower.
+// the root, and twice the waves made them 15 % (refined 39 %) slower. Refined
+// calls keep them too: a wave lists its share's pairs for the FP64 decisions,
+// and longer lists fill its lanes better (hair 399 against 438 us per 10^6
+// pairs, 500,009 degenerate pairs 1.14 against 1.34 ms).
 int64_t single_call_waves(const DeviceInfo &d, int mode, const Args &)
 {
     const bool cand = mode == kCandVariant || mode == kCandVariant + 1;
-    return (cand ? 1 : 2) * (int64_t)d.fused_resident[mode] * d.cus;
+    const bool refine = mode == kConservative || mode == kQuadVariant + kConservative;
+    return (cand || refine ? 1 : 2) * (int64_t)d.fused_resident[mode] * d.cus;
 }
 
 // Enqueue one single call on `s`: the fiber records (when `aos` is given and
 // `convert`), then one persistent launch of about one wave per 64 pairs, at
 // most `max_waves`.
-int launch(int mode, const Args &a, int64_t max_waves, float *aos, hipStream_t s, bool convert = true)
+int launch(const DeviceInfo &d, int mode, const Args &a, float *aos, hipStream_t s, bool convert = true)
 {
+    const int64_t max_waves = single_call_waves(d, mode, a);
     if (aos && convert)
         hipLaunchKernelGGL(k_fibers_aos, dim3((unsigned)((a.n_fibers + 255) / 256)), dim3(256), 0, s,
                            a.fibers, a.fiber_stride, a.n_fibers, (float4 *)aos);
@@ -2077,7 +2432,7 @@ int launch_with_workspace(int mode, const Args &a, void *workspace, size_t works
     // quadratic tables are read in place (the records hold cubic rows)
     const size_t rec = quad ? 0 : record_bytes(a.n_pairs, a.n_fibers, a.pair_fiber != nullptr);
     float *aos = rec && workspace && workspace_bytes >= rec ? (float *)workspace : nullptr;
-    return launch(mode, a, single_call_waves(*d, mode, a), aos, (hipStream_t)stream);
+    return launch(*d, mode, a, aos, (hipStream_t)stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -2259,7 +2614,7 @@ int fiber_intersect_pairs_noalloc(const float *rays, int64_t ray_stride, int64_t
            refine ? t64_out : nullptr, refine ? u64_out : nullptr, normal_out};
     // the fiber records of a gathered call go to this device's copy of the
     // scratch array (through its device address, never the array's name)
-    return launch(mode, a, single_call_waves(*d, mode, a), rec ? d->scratch : nullptr, (hipStream_t)stream);
+    return launch(*d, mode, a, rec ? d->scratch : nullptr, (hipStream_t)stream);
 }
 
 int fiber_intersect_counts(const float *rays, int64_t ray_stride, int64_t n_rays,
@@ -2328,7 +2683,7 @@ int fiber_intersect_candidates(const float *rays, int64_t ray_stride, int64_t n_
     // candidate against the ray shortened to its nearest hit of rounds < k
     for (int32_t k = 0; k < max_candidates; ++k) {
         a.cand_round = k;
-        const int st = launch(mode, a, single_call_waves(*d, mode, a), aos, s, k == 0);
+        const int st = launch(*d, mode, a, aos, s, k == 0);
         if (st != FI_OK) return st;
     }
     return FI_OK;
