@@ -1935,6 +1935,106 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
     }
 }
 
+// Shared searches. Once a wave has no more pairs to start, its free lanes take
+// pending siblings off its busy lanes: a lane hands over the shallowest one
+// (which it would visit last), and the helper rebuilds that node as a backtrack
+// would. The nodes of a pair are then visited at the same time instead of one
+// after another, with the same arithmetic; the result is that of the first leaf
+// in the order of the search. `order` is a lane's place in it: a helper's is
+// its donor's and the bit of the level handed over, since it comes after all
+// that is left of its donor and before the donor's earlier helpers (what a lane
+// hands over lies ever deeper). `group` labels the pair (the lane that had it
+// first), and `stop` is the first leaf's place so far. A leaf before it writes
+// its result over the later one's, and the lanes behind it end; every pair
+// starts as a miss, so that a lane that misses just ends.
+// What bounds the end of a call is its longest pair: a trip of a wave alone on
+// its SIMD takes 0.7 to 1 us, and a few pairs in a million need a hundred and
+// more (degenerate ones up to 850). A trip with a rebuild takes two to three
+// times as long, so sharing starts once a wave has run 32 trips since its last
+// pair and takes place at every second trip (from 20 on: 2^20 mixed pairs at
+// depth 22 take 230 instead of 214 us, from 48 on 299,993 quadratic pairs 91
+// instead of 80; at every trip the former take 234): a call whose longest
+// search ends soon after loses up to 11 us, others gain. Mean of 6 inputs,
+// without and with it: the mixed pairs 341 -> 214 us, the quadratic ones
+// 122 -> 80, 99,991 mixed pairs at depth 16 94 -> 80, 500,009 refined
+// degenerate pairs 1249 -> 798. The trips are those of the loop for pairs of
+// their own: a second loop behind it cost every call 1 to 2 %.
+#ifndef FIBERHIT_LONG_SEARCH
+#define FIBERHIT_LONG_SEARCH 32                // build knob: trips without a new pair after which searches are shared
+#endif
+constexpr int kLongSearch = FIBERHIT_LONG_SEARCH;
+
+struct Shared {                                // in LDS, where the queue was
+    uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave];
+    float root[16 * kWave];                    // the groups' roots, in columns
+};
+
+__device__ __forceinline__ void start_sharing(const Lane &L, Shared &sh)
+{
+    const uint32_t lane = threadIdx.x;
+    sh.order[lane] = 0;
+    sh.group[lane] = lane;
+    sh.stop[lane] = 0xffffffffu;
+    lds_put(sh.root + lane, L.root);
+    __syncthreads();
+}
+
+// Free lanes take pending siblings, one per donor. A sibling close to the
+// leaves is not worth the rebuild.
+__device__ __forceinline__ void share_work(Lane &L, bool &active, Shared &sh)
+{
+    const uint32_t top = L.bits ? 0x80000000u >> __builtin_clz(L.bits) : 0u;
+    const bool donor = active && top > 4u * L.min_size;
+    const uint64_t dm = __ballot(donor), fm = __ballot(!active);
+    if (dm == 0 || fm == 0) return;
+    const int lane = (int)threadIdx.x;
+    const int rd = (int)lanes_below(dm), rf = (int)lanes_below(fm);
+    const int k = min(__popcll(dm), __popcll(fm));
+    if (donor && rd < k) sh.donor[rd] = (uint32_t)lane;
+    __syncthreads();
+    const bool taker = !active && rf < k;
+    const int from = taker ? (int)sh.donor[rf] : lane;
+    const uint32_t bits = __shfl(top, from), start = __shfl(L.start, from), min_size = __shfl(L.min_size, from);
+    const int pair = __shfl(L.pair, from), scene = __shfl(L.scene, from);
+    const float tmax = __shfl(L.tmax, from), slack = __shfl(L.slack, from);
+    if (donor && rd < k) L.bits ^= top;
+    if (taker) {
+        L.bits = bits;
+        L.start = start;
+        L.min_size = min_size;
+        L.pair = pair;
+        L.scene = scene;
+        L.tmax = tmax;
+        L.slack = slack;
+        L.size = kRootSize;
+        L.cached = 0;
+        L.waiting = 0;
+        L.trips = 0;
+        sh.order[lane] = sh.order[from] | bits;
+        const uint32_t group = sh.group[from];
+        sh.group[lane] = group;
+        lds_get(sh.root + group, L.root);
+        active = true;                         // its interval is empty: the next trip backtracks to the sibling
+    }
+    __syncthreads();
+}
+
+// End of a trip of shared searches: does this lane, at a leaf, come before all
+// leaves reached so far? The lanes behind a leaf end.
+__device__ __forceinline__ bool first_leaf(bool &active, bool leaf, Shared &sh)
+{
+    if (__ballot(leaf) == 0) return false;
+    const int lane = (int)threadIdx.x;
+    const uint32_t order = sh.order[lane];
+    uint32_t *stop = &sh.stop[sh.group[lane]];
+    if (leaf) __hip_atomic_fetch_min(stop, order, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    const uint32_t first = *stop;
+    __syncthreads();
+    if (order > first) active = false;
+    return leaf && order == first;
+}
+
 #ifndef FIBERHIT_WAVES
 #define FIBERHIT_WAVES 4                      // build knob: register budget (waves per SIMD)
 #endif
@@ -1945,12 +2045,16 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
 {
     __shared__ float s_cache[16 * kWave];
     __shared__ float s_queue[kQWords * kQueue];
-    static_assert(kQWords * kQueue >= kList && 16 * kWave >= kList, "refine_range lists its pairs there");
+    static_assert(sizeof(Shared) <= sizeof(s_queue) && kQWords * kQueue >= kList && 16 * kWave >= kList, "refine_range lists its pairs there");
     const int lane = (int)threadIdx.x;
     float *col = s_cache + lane;
     const int64_t w = blockIdx.x, waves = gridDim.x;
     int64_t next, end;                                                  // wave-uniform range
     wave_range(w, waves, count, next, end);
+    // what of it is not prepared yet: 32 bits, so that the test of every trip
+    // takes scalar instructions (64-bit ones compare in vector registers; 2^24
+    // hair pairs 1888 -> 1848 us)
+    int left = end > next ? (int)(end - next) : 0;
     const RegRoot root{};
     // batched: pairs are numbered across the scene table; the wave's share
     // is contiguous, so the scene of its next pair only moves forward
@@ -1968,12 +2072,30 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     L.lo = INFINITY;                                                   // an empty interval: no work
     L.hi = -INFINITY;
     bool active = false;
+    // counted searches stay as they are, and so do candidate lists (a list's
+    // hit counts if it is nearer than the one before)
+    constexpr bool kShared = MODE != kCount && !CAND;
+    Shared &sh = *(Shared *)s_queue;
+    int tail = 0;                        // trips since the wave's last pair was started
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
-        if (next < end && q_count < n_free) {
+        if ((left | q_count) == 0) {
+            if (n_free == kWave) break;
+            if (kShared && ++tail >= kLongSearch) {
+                if (tail == kLongSearch) {
+                    start_sharing(L, sh);
+                    if (active) {
+                        if constexpr (BATCHED) finish<MODE>(scenes[L.scene], L.pair, L, false);
+                        else finish<MODE>(a0, L.pair, L, false);
+                    }
+                }
+                if (((tail - kLongSearch) & 1) == 0) share_work(L, active, sh);
+            }
+        }
+        if (left != 0 && q_count < n_free) {
             // setup round: lane k prepares pair next + k
-            const int take = end - next < kQueue - q_count ? (int)(end - next) : kQueue - q_count;
+            const int take = left < kQueue - q_count ? left : kQueue - q_count;
             bool queued = false;
             Node r = {};
             float rlo = 0.0f, rhi = 0.0f, rtmax = 0.0f;
@@ -2047,6 +2169,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
             }
             q_count += __popcll(qm);
             next += take;
+            left -= take;
             if constexpr (BATCHED) {
                 if (next < count && next >= bound0) {
                     while (scene0 + 1 < n_scenes && offsets[scene0 + 1] <= next) ++scene0;
@@ -2096,10 +2219,12 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         // registers; a bypass edge had made the compiler copy the node and
         // the traversal state at every trip (about 45 moves, measured 12-14 %
         // of the call).
-        if (__ballot(active) == 0 && next >= end && q_count == 0) break;
         HitGeo hg;
         const int st = trip<MODE, QUAD, PC, CAND>(L, root, col, hg);
-        if (active && st != kGoOn && !(MODE == kConservative && L.waiting)) {
+        const bool done = active && st != kGoOn && !(MODE == kConservative && L.waiting);
+        bool decides = done;
+        if (kShared && tail >= kLongSearch) decides = first_leaf(active, done && st == kHit, sh);
+        if (decides) {
             if constexpr (BATCHED) {
                 // lanes of the wave's current scene read its output
                 // pointers with uniform loads; others (a scene boundary
@@ -2109,8 +2234,8 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
             } else {
                 finish<MODE, CAND>(a0, L.pair, L, st == kHit, hg);
             }
-            active = false;
         }
+        if (done) active = false;
         if constexpr (MODE == kConservative && CAND) {
             // the FP64 searches run for all parked lanes at once (SIMD lanes
             // of one call) when no busy lane is left: every lane of the wave
@@ -2149,11 +2274,14 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         }
     }
     if constexpr (MODE == kConservative && !CAND) {
+        // the arguments are read again from where the launch put them: kept
+        // for after the loop they had pushed others out of the scalar registers
+        const Args *args = (const Args *)__builtin_amdgcn_kernarg_segment_ptr();
         // the wave's own marks, written above by other lanes
         __threadfence_block();
         __syncthreads();
         wave_range(w, waves, count, next, end);
-        refine_range<BATCHED, QUAD>(a0, scenes, offsets, n_scenes, next, end, aos, (int *)s_cache, (int *)s_queue);
+        refine_range<BATCHED, QUAD>(*args, scenes, offsets, n_scenes, next, end, aos, (int *)s_cache, (int *)s_queue);
     }
 }
 
