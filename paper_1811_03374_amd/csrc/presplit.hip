@@ -497,9 +497,11 @@ __global__ __launch_bounds__(kBlock) void k_validate(const float *F, int64_t fs,
 // found sets the bit of its start (in units of 2^-max_level) in its fiber's
 // bitmap, which orders the pieces whatever order they were found in.
 // 131,072 degenerate curves to level 6 took 15.6 ms (count) and 27.8 ms
-// (write) with one lane walking each fiber's tree by itself; now 0.87
-// and 1.55 ms.
-// Bound by the latency of FP64 chains (two waves a SIMD at that size).
+// (write) with one lane walking each fiber's tree by itself; now 0.8 and
+// 1.3 ms.
+// Bound by the latency of FP64 chains. Their registers are held to 256, for two
+// waves a SIMD: without a limit the compiler took more, and 131,072 curves
+// 2346 us instead of 2128 (for three waves 2181, for four 2203).
 constexpr int kWave = 64;
 #ifndef FIBERHIT_NODE_STACK
 #define FIBERHIT_NODE_STACK 1024                // build knob: node stack entries of a wave
@@ -646,7 +648,7 @@ __device__ __forceinline__ int map_count(const WalkLds<NF> &s, int f, int max_le
 }
 
 template <int NF>
-__global__ __launch_bounds__(kWave) void k_presplit_count(const float *F, int64_t fs, int64_t n, int max_level,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_presplit_count(const float *F, int64_t fs, int64_t n, int max_level,
                                                           int64_t *counts)
 {
     __shared__ WalkLds<NF> s;
@@ -662,7 +664,7 @@ __global__ __launch_bounds__(kWave) void k_presplit_count(const float *F, int64_
 // finding its piece in the bitmaps: consecutive lanes write consecutive
 // columns. A fiber with one piece is not walked again.
 template <int NF>
-__global__ __launch_bounds__(kWave) void k_presplit_write(const float *F, int64_t fs, int64_t n, int max_level,
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_presplit_write(const float *F, int64_t fs, int64_t n, int max_level,
                                                           const int64_t *offsets, int64_t n_pieces, float *P,
                                                           int64_t ps, int32_t *pfiber, float *pu0, float *pu1,
                                                           int32_t *pmask)
