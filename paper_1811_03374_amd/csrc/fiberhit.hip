@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdlib>
@@ -276,11 +277,11 @@ struct Args {
     int32_t *counts;                       // counting mode
     double *t64_out; double *u64_out;      // refinement
     float *normal_out;                     // normals (3 rows of n_pairs), or null
-    // candidate lists: pair i is ray i against its candidate number
-    // cand_round (cand_fiber[cand_off[i] + cand_round]), tested against the
-    // ray shortened to the nearest hit so far; pair_depth then indexes the
-    // candidates. Null cand_off: plain pairs.
-    const int64_t *cand_off; const int32_t *cand_fiber; int32_t cand_round; int64_t n_cand;
+    // candidate lists: pair i is ray i against one candidate after another,
+    // from number cand_first on (cand_fiber[cand_off[i] + cand_first]), each
+    // tested against the ray shortened to the nearest hit so far; pair_depth
+    // then indexes the candidates. Null cand_off: plain pairs.
+    const int64_t *cand_off; const int32_t *cand_fiber; int32_t cand_first; int64_t n_cand;
     int32_t *fiber_out;                    // the fiber of each ray's nearest hit
 };
 
@@ -1544,6 +1545,25 @@ __device__ __forceinline__ void leaf_normal(const Args &a, int64_t i, const Lane
     nz = (float)(wz * in);
 }
 
+// Candidate lists start as misses (each position then writes the hits).
+template <int MODE>
+__device__ __forceinline__ void cand_init(const Args &a, int64_t i)
+{
+    a.t_out[i] = INFINITY;
+    a.u_out[i] = __builtin_nanf("");
+    a.hit_out[i] = 0;
+    a.fiber_out[i] = -1;
+    if (MODE == kConservative) {
+        a.t64_out[i] = INFINITY;
+        a.u64_out[i] = __builtin_nan("");
+    }
+    if (a.normal_out) {
+        a.normal_out[i] = __builtin_nanf("");
+        a.normal_out[a.n_pairs + i] = __builtin_nanf("");
+        a.normal_out[2 * a.n_pairs + i] = __builtin_nanf("");
+    }
+}
+
 // Write the result of pair i (Section 3.3: u from projecting the hit point
 // onto the leaf chord; hit when t < tmax). A refined pair (depth > 16 under
 // FI_FP64_REFINE) reports its FP64 surface hit, decided in FP64.
@@ -1554,7 +1574,7 @@ __device__ __forceinline__ void leaf_normal(const Args &a, int64_t i, const Lane
 constexpr uint8_t kToRefine = 2;               // hit_out of a pair that refine_range decides
 template <int MODE, bool CAND = false>
 __device__ __forceinline__ void finish(const Args &a, int64_t i, const Lane &L, bool reached,
-                                       HitGeo hg = HitGeo{}, Refined ref = Refined{})
+                                       HitGeo hg = HitGeo{}, Refined ref = Refined{}, int round = 0)
 {
     float t = INFINITY, u = __builtin_nanf("");
     double t64 = INFINITY, u64 = __builtin_nan("");
@@ -1584,7 +1604,7 @@ __device__ __forceinline__ void finish(const Args &a, int64_t i, const Lane &L, 
         // candidate lists: a miss leaves the ray's nearest hit so far; a
         // hit (nearer by construction: tmax was shortened to it) replaces it
         if (!hit) return;
-        a.fiber_out[i] = a.cand_fiber[a.cand_off[i] + a.cand_round];
+        a.fiber_out[i] = a.cand_fiber[a.cand_off[i] + a.cand_first + round];
     }
     a.t_out[i] = t;
     a.u_out[i] = u;
@@ -1686,18 +1706,18 @@ __device__ __forceinline__ void load_rows(const float *p, int64_t stride, float 
 // k_fibers_aos): a gathered fiber is then one or two cache lines instead of
 // one line per coordinate row.
 // In candidate mode (cand_off given) pair i is ray i against its candidate
-// number cand_round; a ray without that candidate, or with an invalid one,
+// number cand_first + round; a ray without that candidate, or with an invalid one,
 // is a definite miss too (its callers then leave the ray's nearest hit so far
 // as it is), and tmax is the ray's tmax shortened to that hit.
 // QUAD: the fiber table holds quadratics (12 rows: p0, p1, p2), loaded as
 // their exact cubic elevation (t0 = 2/3 (p1 - p0), t1 = 2/3 (p2 - p1)).
 template <bool CAND, bool QUAD = false>
 __device__ __forceinline__ bool load_pair(const Args &a, int64_t i, float *q, float &tmax, uint32_t &depth,
-                                          const float *aos)
+                                          const float *aos, int round = 0)
 {
     int64_t ri, fi;
     if constexpr (CAND) {
-        const int64_t o = a.cand_off[i] + a.cand_round;
+        const int64_t o = a.cand_off[i] + a.cand_first + round;
         if (o >= a.cand_off[i + 1] || o < 0 || o >= a.n_cand) return false;
         ri = i;
         fi = a.cand_fiber[o];
@@ -2035,6 +2055,31 @@ __device__ __forceinline__ bool first_leaf(bool &active, bool leaf, Shared &sh)
     return leaf && order == first;
 }
 
+// Candidate lists. A ray's candidates are tested one after another, each against
+// the ray shortened to its nearest hit so far; a wave keeps its rays from the
+// first candidate to the last. A ray whose search has ended waits, if its list
+// goes on, in a ring in LDS until a setup round prepares its next candidate
+// beside others (and beside the first ones of new rays). Up to 128 rays of a
+// wave are under way (64 searched, 64 in the queue), so that the ring has room
+// for all of them. Bound by the same trips as single calls, and by the longest
+// list of a small call. A setup round waits for 8 rays, or for the wave's last
+// search (16: 304 instead of 285 us for 2^18 hair lists, 126 instead of 131 for
+// 65,537 mixed ones; 32: 319 and 176).
+// One launch for each position of the lists, with the lanes that were done idle
+// until the longest search of the position had ended, took 642 and 429 us, and
+// 1333 instead of 242 for 65,536 refined lists.
+#ifndef FIBERHIT_READY
+#define FIBERHIT_READY 8                      // build knob: rays a setup round waits for
+#endif
+constexpr int kReady = FIBERHIT_READY;
+constexpr int32_t kMaxRounds = 1 << 24;        // candidates of a list a launch tests
+
+struct Waiting {                               // a ring
+    int ray[2 * kWave], round[2 * kWave];
+};
+
+__device__ __forceinline__ int wslot(int k) { return k & (2 * kWave - 1); }
+
 #ifndef FIBERHIT_WAVES
 #define FIBERHIT_WAVES 4                      // build knob: register budget (waves per SIMD)
 #endif
@@ -2049,6 +2094,9 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     const int lane = (int)threadIdx.x;
     float *col = s_cache + lane;
     const int64_t w = blockIdx.x, waves = gridDim.x;
+    __shared__ int s_waiting[CAND ? 4 * kWave : 1];
+    static_assert(!CAND || sizeof(Waiting) == sizeof(s_waiting), "rays between two candidates");
+    Waiting &waiting = *(Waiting *)s_waiting;
     int64_t next, end;                                                  // wave-uniform range
     wave_range(w, waves, count, next, end);
     // what of it is not prepared yet: 32 bits, so that the test of every trip
@@ -2067,6 +2115,8 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         base0 = uniform_i64(offsets[scene0]);
         bound0 = uniform_i64(offsets[scene0 + 1]);
     }
+    const int rounds = CAND ? n_scenes : 0;                             // candidates tested of a list
+    int w_head = 0, w_count = 0;         // the rays that wait for their next candidate
     int q_head = 0, q_count = 0;         // the queue: entries q_head .. q_head + q_count - 1 (mod kQueue)
     Lane L = {};
     L.lo = INFINITY;                                                   // an empty interval: no work
@@ -2080,34 +2130,70 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
-        if ((left | q_count) == 0) {
-            if (n_free == kWave) break;
-            if (kShared && ++tail >= kLongSearch) {
-                if (tail == kLongSearch) {
-                    start_sharing(L, sh);
-                    if (active) {
-                        if constexpr (BATCHED) finish<MODE>(scenes[L.scene], L.pair, L, false);
-                        else finish<MODE>(a0, L.pair, L, false);
+        int take = 0, from = 0, round = 0;
+        bool setup = false;
+        if constexpr (CAND) {
+            if ((left | q_count | w_count) == 0 && n_free == kWave) break;
+            // new rays as far as the ring has room for all that are under way
+            const int room = 2 * kWave - w_count - q_count - (kWave - n_free);
+            const int n_ready = w_count + (left < room ? left : room);
+            setup = n_ready >= kReady ? q_count < n_free : n_ready > 0 && q_count == 0 && n_free == kWave;
+            from = w_count < kQueue - q_count ? w_count : kQueue - q_count;
+            take = kQueue - q_count - from;
+            take = take < room ? take : room;
+            take = take < left ? take : left;
+        } else {
+            if ((left | q_count) == 0) {
+                if (n_free == kWave) break;
+                if (kShared && ++tail >= kLongSearch) {
+                    if (tail == kLongSearch) {
+                        start_sharing(L, sh);
+                        if (active) {
+                            if constexpr (BATCHED) finish<MODE>(scenes[L.scene], L.pair, L, false);
+                            else finish<MODE>(a0, L.pair, L, false);
+                        }
                     }
+                    if (((tail - kLongSearch) & 1) == 0) share_work(L, active, sh);
                 }
-                if (((tail - kLongSearch) & 1) == 0) share_work(L, active, sh);
             }
         }
-        if (left != 0 && q_count < n_free) {
-            // setup round: lane k prepares pair next + k
-            const int take = left < kQueue - q_count ? left : kQueue - q_count;
+        if (CAND ? setup : left != 0 && q_count < n_free) {
+            // setup round: lane k prepares pair next + k, or (candidate lists)
+            // the next candidate of a ray that waits or the first of a new one
+            bool prepares = false, more = false;
+            int64_t idx = next + lane;
+            if constexpr (CAND) {
+                __threadfence_block();             // the hits of other lanes (t_out)
+                prepares = lane < from + take;
+                idx = 0;
+                if (prepares) {
+                    if (lane < from) {
+                        idx = waiting.ray[wslot(w_head + lane)];
+                        round = waiting.round[wslot(w_head + lane)];
+                    } else {
+                        idx = next + (lane - from);
+                        if (a0.cand_first == 0) cand_init<MODE>(a0, idx);
+                    }
+                    const int64_t len = a0.cand_off[idx + 1] - a0.cand_off[idx] - a0.cand_first;
+                    prepares = round < rounds && round < len;
+                    more = round + 1 < rounds && round + 1 < len;
+                }
+                w_head = wslot(w_head + from);
+                w_count -= from;
+            } else {
+                take = left < kQueue - q_count ? left : kQueue - q_count;
+            }
             bool queued = false;
             Node r = {};
             float rlo = 0.0f, rhi = 0.0f, rtmax = 0.0f;
             uint32_t depth = 0;
-            int64_t idx = next + lane;
-            int sc = scene0;
+            int sc = CAND ? 2 * round + (more ? 1 : 0) : scene0;
             // each preparing lane stages its root in the queue entry after the
             // current tail plus its lane number; survivors then move to
             // consecutive entries (every lane has read its own entry back
             // before any lane writes)
             float *stage = s_queue + qslot(q_head + q_count + lane);
-            if (lane < take) {
+            if (CAND ? prepares : lane < take) {
                 Args a = a0;
                 if constexpr (BATCHED) {
                     if (idx < bound0) {
@@ -2119,7 +2205,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                         a = scenes[sc];
                     }
                 }
-                const bool ok = load_pair<CAND, QUAD>(a, idx, stage, rtmax, depth, aos);
+                const bool ok = load_pair<CAND, QUAD>(a, idx, stage, rtmax, depth, aos, round);
                 asm volatile("" ::: "memory");
                 float *f = &r.p.x;
 #pragma unroll
@@ -2147,7 +2233,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                         D.level = 0;
                         D.trips = 1;
                         D.slack = slack;
-                        finish<MODE, CAND>(a, idx, D, vis, hit_geo(r, D.t, te < lu));
+                        finish<MODE, CAND>(a, idx, D, vis, hit_geo(r, D.t, te < lu), Refined{}, round);
                     }
                 }
             }
@@ -2170,6 +2256,16 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
             q_count += __popcll(qm);
             next += take;
             left -= take;
+            if constexpr (CAND) {
+                const bool again = prepares && !queued && more;
+                const uint64_t am = __ballot(again);
+                if (again) {
+                    const int e = wslot(w_head + w_count + (int)lanes_below(am));
+                    waiting.ray[e] = (int)idx;
+                    waiting.round[e] = round + 1;
+                }
+                w_count += __popcll(am);
+            }
             if constexpr (BATCHED) {
                 if (next < count && next >= bound0) {
                     while (scene0 + 1 < n_scenes && offsets[scene0 + 1] <= next) ++scene0;
@@ -2232,10 +2328,12 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                 if (L.scene == scene0) finish<MODE>(cur, L.pair, L, st == kHit, hg);
                 else finish<MODE>(scenes[L.scene], L.pair, L, st == kHit, hg);
             } else {
-                finish<MODE, CAND>(a0, L.pair, L, st == kHit, hg);
+                finish<MODE, CAND>(a0, L.pair, L, st == kHit, hg, Refined{}, L.scene >> 1);
             }
         }
         if (done) active = false;
+        bool again = CAND && done && (L.scene & 1);       // candidate lists: the ray has another candidate
+        const int ray = L.pair, at = L.scene >> 1;
         if constexpr (MODE == kConservative && CAND) {
             // the FP64 searches run for all parked lanes at once (SIMD lanes
             // of one call) when no busy lane is left: every lane of the wave
@@ -2249,7 +2347,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                     const float *rays = a0.rays, *fibers = a0.fibers;
                     const int64_t rs = a0.ray_stride, fs = a0.fiber_stride;
                     // the ray's tmax shortened to its FP64 nearest hit so far
-                    const int64_t fi = a0.cand_fiber[a0.cand_off[L.pair] + a0.cand_round];
+                    const int64_t fi = a0.cand_fiber[a0.cand_off[L.pair] + a0.cand_first + at];
                     const double tlim = fmin((double)rays[6 * rs + L.pair], a0.t64_out[L.pair]);
                     const int32_t pair = L.pair;
                     const Refined r = refine_whole_curve(rays, rs, fibers, fs, pair, fi, tlim, L.t, L.ru,
@@ -2258,14 +2356,24 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                     // live across it); a refined pair's finish reads only the
                     // search's result from the lane (slack >= 0)
                     Lane R = {};
-                    finish<MODE, CAND>(a0, pair, R, r.hit, HitGeo{}, r);
+                    finish<MODE, CAND>(a0, pair, R, r.hit, HitGeo{}, r, at);
                     active = false;
+                    again = (L.scene & 1) != 0;
                 }
                 // every lane is free now. Its traversal state is reset, so
                 // that none of it is live across the searches (kept, it
                 // had to be saved and restored around the call)
                 L = Lane{};
             }
+        }
+        if constexpr (CAND) {
+            const uint64_t am = __ballot(again);
+            if (again) {
+                const int e = wslot(w_head + w_count + (int)lanes_below(am));
+                waiting.ray[e] = ray;
+                waiting.round[e] = at + 1;
+            }
+            w_count += __popcll(am);
         }
         if (!active) {
             L.lo = INFINITY;
@@ -2296,27 +2404,6 @@ __global__ __launch_bounds__(256) void k_fibers_aos(const float *F, int64_t fs, 
     for (int k = 0; k < 4; ++k)
         out[4 * f + k] = make_float4(F[(4 * k) * fs + f], F[(4 * k + 1) * fs + f], F[(4 * k + 2) * fs + f],
                                      F[(4 * k + 3) * fs + f]);
-}
-
-// Candidate lists start as misses (each round then writes the hits).
-__global__ __launch_bounds__(256) void k_cand_init(int64_t n, float *t, float *u, uint8_t *hit, int32_t *fiber,
-                                                   double *t64, double *u64, float *nrm)
-{
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    t[i] = INFINITY;
-    u[i] = __builtin_nanf("");
-    hit[i] = 0;
-    fiber[i] = -1;
-    if (t64) {
-        t64[i] = INFINITY;
-        u64[i] = __builtin_nan("");
-    }
-    if (nrm) {
-        nrm[i] = __builtin_nanf("");
-        nrm[n + i] = __builtin_nanf("");
-        nrm[2 * n + i] = __builtin_nanf("");
-    }
 }
 
 int check_common(const float *rays, int64_t ray_stride, int64_t n_rays,
@@ -2554,19 +2641,19 @@ int64_t single_call_waves(const DeviceInfo &d, int mode, const Args &)
     return (cand || refine ? 1 : 2) * (int64_t)d.fused_resident[mode] * d.cus;
 }
 
-// Enqueue one single call on `s`: the fiber records (when `aos` is given and
-// `convert`), then one persistent launch of about one wave per 64 pairs, at
-// most `max_waves`.
-int launch(const DeviceInfo &d, int mode, const Args &a, float *aos, hipStream_t s, bool convert = true)
+// Enqueue one single call on `s`: the fiber records (when `aos` is given), then
+// one persistent launch of about one wave per 64 pairs, at most `max_waves`.
+// `rounds`: how many candidates of each list it tests (candidate lists).
+int launch(const DeviceInfo &d, int mode, const Args &a, float *aos, hipStream_t s, int rounds = 0)
 {
     const int64_t max_waves = single_call_waves(d, mode, a);
-    if (aos && convert)
+    if (aos && a.cand_first == 0)
         hipLaunchKernelGGL(k_fibers_aos, dim3((unsigned)((a.n_fibers + 255) / 256)), dim3(256), 0, s,
                            a.fibers, a.fiber_stride, a.n_fibers, (float4 *)aos);
     int64_t g = (a.n_pairs + kWave - 1) / kWave;
     if (g > max_waves) g = max_waves;
     if (g > 0)
-        hipLaunchKernelGGL(kFused[mode], dim3((unsigned)g), dim3(kWave), 0, s, a, nullptr, nullptr, 0,
+        hipLaunchKernelGGL(kFused[mode], dim3((unsigned)g), dim3(kWave), 0, s, a, nullptr, nullptr, rounds,
                            a.n_pairs,
                            mode == kConservative || mode == kCandVariant + 1 ||
                                    mode == kQuadVariant + kConservative
@@ -2826,9 +2913,6 @@ int fiber_intersect_candidates(const float *rays, int64_t ray_stride, int64_t n_
     const int ds = device_info(d);
     if (ds != FI_OK) return ds;
     const hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_cand_init, dim3((unsigned)((n_rays + 255) / 256)), dim3(256), 0, s, n_rays, t_out, u_out,
-                       hit_out, fiber_out, refine ? t64_out : nullptr, refine ? u64_out : nullptr, normal_out);
-    if (hipGetLastError() != hipSuccess) return FI_ERR_HIP;
     const int mode = refine ? kCandVariant + 1 : kCandVariant;
     Args a{rays, ray_stride, n_rays, fibers, fiber_stride, n_fibers,
            nullptr, nullptr, cand_depth, depth, n_rays, t_out, u_out, hit_out, nullptr,
@@ -2836,13 +2920,13 @@ int fiber_intersect_candidates(const float *rays, int64_t ray_stride, int64_t n_
            cand_offsets, cand_fiber, 0, n_candidates, fiber_out};
     const size_t rec = record_bytes(n_candidates, n_fibers, true);
     float *aos = rec && workspace && workspace_bytes >= rec ? (float *)workspace : nullptr;
-    // one launch per list position, in order: round k tests every ray's k-th
-    // candidate against the ray shortened to its nearest hit of rounds < k
-    for (int32_t k = 0; k < max_candidates; ++k) {
-        a.cand_round = k;
-        const int st = launch(*d, mode, a, aos, s, k == 0);
+    // one launch (a lane holds a candidate's place in its list in 24 bits)
+    do {
+        const int32_t rounds = std::min(max_candidates - a.cand_first, kMaxRounds);
+        const int st = launch(*d, mode, a, aos, s, rounds);
         if (st != FI_OK) return st;
-    }
+        a.cand_first += rounds;
+    } while (a.cand_first < max_candidates);
     return FI_OK;
 }
 
