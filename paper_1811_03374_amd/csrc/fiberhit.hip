@@ -2641,12 +2641,21 @@ int64_t single_call_waves(const DeviceInfo &d, int mode, const Args &)
     return (cand || refine ? 1 : 2) * (int64_t)d.fused_resident[mode] * d.cus;
 }
 
-// Enqueue one single call on `s`: the fiber records (when `aos` is given), then
-// one persistent launch of about one wave per 64 pairs, at most `max_waves`.
-// `rounds`: how many candidates of each list it tests (candidate lists).
+constexpr int64_t kRowPairs = 1 << 16;
+
+// Enqueue one single call on `s`: the fiber records (when `aos` is given and the
+// pairs are many), then one persistent launch of about one wave per 64 pairs,
+// at most `max_waves`. `rounds`: how many candidates of each list it tests
+// (candidate lists).
 int launch(const DeviceInfo &d, int mode, const Args &a, float *aos, hipStream_t s, int rounds = 0)
 {
     const int64_t max_waves = single_call_waves(d, mode, a);
+    // Few pairs read the rows: the records' pass takes 2 to 3 us of the call
+    // before its first pair. 4096 pairs of 64 fibers 23.0 -> 20.8 us, 65,536
+    // hair pairs over 4000 segments 27.7 -> 26.4 and over 65,536 the same
+    // (37.3); at 2^18 pairs the records are the faster way (45.7 against 49.7
+    // over 1000 segments), and at 65,537 candidate lists (97 against 106).
+    if (!a.cand_off && a.n_pairs <= kRowPairs) aos = nullptr;
     if (aos && a.cand_first == 0)
         hipLaunchKernelGGL(k_fibers_aos, dim3((unsigned)((a.n_fibers + 255) / 256)), dim3(256), 0, s,
                            a.fibers, a.fiber_stride, a.n_fibers, (float4 *)aos);
