@@ -4,7 +4,10 @@ hipcc cross-compiles for gfx950 on a machine without a GPU. Flags:
   -ffp-contract=off   every FMA in the kernels is explicit, so identical
                       expressions round identically wherever they appear;
   -Xclang -target-feature -Xclang -packed-fp32-ops
-                      no packed FP32 instructions are generated.
+                      no packed FP32 instructions are generated;
+  -falign-loops=64    loops start at an instruction cache line: the traversal
+                      loop takes up to 2 % longer where it does not (2^24 hair
+                      pairs 1842 against 1812 us after a change before it).
 """
 from __future__ import annotations
 
@@ -23,7 +26,7 @@ ARCH = "gfx950"
 
 def hipcc_cmd(out: str, extra=()):
     return ["hipcc", f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
-            "-ffp-contract=off",
+            "-ffp-contract=off", "-falign-loops=64",
             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
             "-Wall", "-Wno-unused-function",
             "-I", os.path.join(ROOT, "include"), *extra, "-o", out, *SRCS]

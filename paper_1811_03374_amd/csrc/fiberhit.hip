@@ -1983,6 +1983,12 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
 #define FIBERHIT_LONG_SEARCH 32                // build knob: trips without a new pair after which searches are shared
 #endif
 constexpr int kLongSearch = FIBERHIT_LONG_SEARCH;
+// Of few pairs the longest search is seldom much longer than that, and they wait
+// 48 trips: mixed pairs at depth 22, 4000 of them 61.6 -> 54.4 us (not shared
+// 57.3), 13,039 75.0 -> 70.1 (74.1), 40,000 87.2 -> 85.1 (86.4); at depth 15
+// 13,039 50.3 -> 48.1 (57.8) but 40,000 61.3 -> 63.5 (73.3), and 99,991 with
+// normals at depth 16 would lose (83 -> 88; 94).
+constexpr int64_t kSmallCall = 1 << 16;
 
 struct Shared {                                // in LDS, where the queue was
     uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave];
@@ -2126,7 +2132,9 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     // hit counts if it is nearer than the one before)
     constexpr bool kShared = MODE != kCount && !CAND;
     Shared &sh = *(Shared *)s_queue;
-    int tail = 0;                        // trips since the wave's last pair was started
+    // trips since the wave's last pair was started (from -16 on in a small
+    // call, see kLongSearch)
+    int tail = count <= kSmallCall ? -16 : 0;
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
