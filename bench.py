@@ -388,8 +388,8 @@ def bench_candidates(args):
             "config": {"workload": "hair candidate lists: 2^20 rays (10% grazing) over 100k strands x 8 "
                                    "segments (+1e3 offset), 6..15 shuffled segments of neighbouring strands "
                                    "per ray", "rays": n, "candidates": nc, "max_candidates": mc,
-                       "launch": "one initialising kernel, then one persistent k_fused launch per list "
-                                 "position (max_candidates launches)"},
+                       "launch": "one persistent k_fused launch (a wave tests its rays' candidates "
+                                 "as they come)"},
             "results": res}
     print(json.dumps(line), flush=True)
 

@@ -169,10 +169,13 @@ size_t fiber_pairs_workspace_bytes(int64_t n_pairs, int64_t n_fibers, int32_t ga
  * no leaf holding part of that solid is pruned; a pair whose search reaches
  * no leaf misses. Once it reaches a leaf, the pair is decided in FP64: the
  * first point of that solid along the ray, t in [0, tmax), over the whole
- * curve (boundary points from Newton's method on <P - C(u), C'(u)> = 0,
- * |P - C(u)| = r(u) started at the FP32 leaf hit, from 64 samples of the
- * disc excess with a bracketed root search at sign changes and a bracketed
- * minimisation at local minima, the end discs, t = 0 for an origin inside).
+ * curve, once its wave's traversal is done: the part of the curve that can lie
+ * within its radius of the ray is found first (most pairs without a hit end
+ * there), then its boundary points <P - C(u), C'(u)> = 0, |P - C(u)| = r(u):
+ * from the closest point on either side where the part is regular and simple,
+ * else from samples of the disc excess (1/64 apart) with a bracketed root
+ * search at sign changes and a bracketed minimisation at local minima; the end
+ * discs; t = 0 for an origin inside.
  * All five outputs then describe that point (hit decided in FP64; hit = 0,
  * t = +inf when there is none). Pairs of depth
  * <= 16 keep the plain method's results; their t64/u64 are the float results
@@ -310,10 +313,10 @@ size_t fiber_candidates_workspace_bytes(int64_t n_candidates, int64_t n_fibers, 
  * NULL); workspace as for fiber_intersect_pairs (size:
  * fiber_candidates_workspace_bytes), or NULL.
  *
- * Implementation: an initialising kernel writes misses, then one persistent
- * launch per list position k (max_candidates launches in stream order), each
- * testing every ray's k-th candidate against the nearest hit of positions
- * before k and writing only hits.
+ * Implementation: one persistent launch. Each wave takes an even share of the
+ * rays, writes their misses and tests their candidates: the next one of a ray
+ * is prepared once the search of the one before has ended, beside those of
+ * other rays.
  *
  * Errors: FI_ERR_NULL (rays, fibers, cand_offsets or an output NULL with
  * n_rays > 0; cand_fiber NULL with n_candidates > 0; t64_out/u64_out under
