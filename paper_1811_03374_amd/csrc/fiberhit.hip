@@ -1971,12 +1971,11 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
 // its SIMD takes 0.7 to 1 us, and a few pairs in a million need a hundred and
 // more (degenerate ones up to 850). A trip with a rebuild takes two to three
 // times as long, so sharing starts once a wave has run 32 trips since its last
-// pair and takes place at every second trip (from 20 on: 2^20 mixed pairs at
-// depth 22 take 230 instead of 214 us, from 48 on 299,993 quadratic pairs 91
-// instead of 80; at every trip the former take 234): a call whose longest
+// pair and takes place at every second trip (from 48 on 299,993 quadratic pairs
+// take 91 instead of 80 us; at every trip 83): a call whose longest
 // search ends soon after loses up to 11 us, others gain. Mean of 6 inputs,
-// without and with it: the mixed pairs 341 -> 214 us, the quadratic ones
-// 122 -> 80, 99,991 mixed pairs at depth 16 94 -> 80, 500,009 refined
+// without and with it: 2^20 mixed pairs at depth 22 343 -> 231 us, the quadratic
+// ones 122 -> 80, 99,991 mixed pairs at depth 16 94 -> 80, 500,009 refined
 // degenerate pairs 1249 -> 798. The trips are those of the loop for pairs of
 // their own: a second loop behind it cost every call 1 to 2 %.
 #ifndef FIBERHIT_LONG_SEARCH
@@ -1989,6 +1988,11 @@ constexpr int kLongSearch = FIBERHIT_LONG_SEARCH;
 // 13,039 50.3 -> 48.1 (57.8) but 40,000 61.3 -> 63.5 (73.3), and 99,991 with
 // normals at depth 16 would lose (83 -> 88; 94).
 constexpr int64_t kSmallCall = 1 << 16;
+// In a large call other waves have the issue slots that a rebuild takes while
+// it is short of its end, and waves wait 64 trips: 2^20 mixed pairs at depth 22
+// whose longest search is short 215 -> 191 us (not shared 200 to 205), six other
+// inputs 216 -> 231 (343). 300,001 pairs take 130 us with 32 trips (196).
+constexpr int64_t kLargeCall = 1 << 19;
 
 struct Shared {                                // in LDS, where the queue was
     uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave];
@@ -2132,9 +2136,9 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     // hit counts if it is nearer than the one before)
     constexpr bool kShared = MODE != kCount && !CAND;
     Shared &sh = *(Shared *)s_queue;
-    // trips since the wave's last pair was started (from -16 on in a small
-    // call, see kLongSearch)
-    int tail = count <= kSmallCall ? -16 : 0;
+    // trips since the wave's last pair was started (from -16 or -32 on in a
+    // small or large call, see kSmallCall)
+    int tail = count <= kSmallCall ? -16 : count > kLargeCall ? -32 : 0;
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
