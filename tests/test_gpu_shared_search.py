@@ -84,3 +84,11 @@ def test_normals_batches_and_lists(long_searches):
     c = binding.intersect_candidates(R, F, off, torch.arange(n, device=DEV, dtype=torch.int32), 22,
                                      max_candidates=1, normal=True)
     assert same((c[0], c[1], c[2], c[4]), (t, u, h, nrm))
+
+
+@pytest.mark.parametrize("n", [1 << 16, (1 << 16) + 1, 1 << 19, (1 << 19) + 1])
+def test_limits_of_call_sizes(n):
+    """Either side of the sizes at which waves wait longer before they share."""
+    w = W.straight_and_curved(n + (n & 1))
+    R, F = g(w.rays)[:, :n], g(w.fibers)[:, :n]
+    assert same(binding.intersect_pairs(R, F, 22), binding.intersect_pairs(R, F, 22, counts=True)[:3])
