@@ -214,6 +214,12 @@ __device__ __forceinline__ void turn(Q16 &q)
 // rounding). Where the start tangent is negligible (the normal is then
 // another edge, and x_1 does not vanish) nothing is claimed; a comparison
 // with NaN claims nothing.
+// The products are of eighth degree in the coordinates: bounds_hold keeps them
+// from overflowing, and where the right side's factors are so small that its
+// square may lose bits to underflow (and the left side may be 0) nothing is
+// claimed.
+constexpr double kLeast = 0x1p-500;
+
 __device__ __forceinline__ bool behind_start(const Q16 &q)
 {
     const double *p = q.v;
@@ -240,7 +246,7 @@ __device__ __forceinline__ bool behind_start(const Q16 &q)
     };
     const double x2 = fmax(4.0 * cross2(d[1]), cross2(d[2]));
     const double rhs = m * A0;
-    return nn > 0x1p-40 * cc && m > 0.0 && A0 > 0.0 && r * r * x2 * cc <= (rhs * rhs) * (1.0 - 1e-6);
+    return nn > 0x1p-40 * cc && A0 > 0.0 && rhs >= kLeast && r * r * x2 * cc <= (rhs * rhs) * (1.0 - 1e-6);
 }
 
 // The same for a later part of the curve (control points q) and the plane
@@ -265,22 +271,28 @@ __device__ __forceinline__ bool part_behind(const Q16 &q, const double *p0, cons
     const double r = fmax(fmax(p[3], p[7]), fmax(fmax(p[11], p[15]), 0.0));
     const double cc = d3(c[0], c[1], c[2], c[0], c[1], c[2]), nn = d3(n[0], n[1], n[2], n[0], n[1], n[2]);
     const double room = a * a * (1.0 - 1e-6);
-    return a > 0.0 && (r * r * nn <= room || (m > 0.0 && r * r * x2 * cc <= room * (m * m)));
+    return a >= kLeast && (r * r * nn <= room || (a * m >= kLeast && r * r * x2 * cc <= room * (m * m)));
 }
 
 // The excess as the search computes it is off by its rounding, up to 2^-49
 // of the coordinates: the bounds stand in for the search only where that is
-// below half the threshold of 1e-9 of the extent.
+// below half the threshold of 1e-9 of the extent, and only for chords between
+// 2^-40 and 2^64, so that products of eighth degree are finite and (but for
+// what cancels) far above the subnormals. Without that, both sides of a bound
+// could be 0 (extents below 2e-41) or infinite (near the largest float32), and
+// thick ends passed as clear.
 __device__ __forceinline__ bool bounds_hold(const Q16 &q)
 {
     const double *p = q.v;
-    double M = 0.0;
+    constexpr double k = 0x1p-48 * 1e9;
+    double M = 0x1p-40 / k;
 #pragma unroll
-    for (int k = 0; k < 16; ++k)
-        if ((k & 3) != 3) M = fmax(M, fabs(p[k]));
+    for (int j = 0; j < 16; ++j)
+        if ((j & 3) != 3) M = fmax(M, fabs(p[j]));
     const double ax = p[12] - p[0], ay = p[13] - p[1], az = p[14] - p[2];
-    M *= 0x1p-48 * 1e9;
-    return d3(ax, ay, az, ax, ay, az) > M * M;
+    const double cc = d3(ax, ay, az, ax, ay, az);
+    M *= k;
+    return cc > M * M && cc <= 0x1p128;
 }
 
 // The ends (bit 5 start, bit 6 end) at which the bounds show that no disc
@@ -299,6 +311,9 @@ __device__ __forceinline__ int ends_clear(const Q16 &q)
 __device__ __forceinline__ bool behind_start_in_parts(const Q16 &q)
 {
     const double n[3] = {q.v[4] - q.v[0], q.v[5] - q.v[1], q.v[6] - q.v[2]};
+    const double c[3] = {q.v[12] - q.v[0], q.v[13] - q.v[1], q.v[14] - q.v[2]};
+    if (!(d3(n[0], n[1], n[2], n[0], n[1], n[2]) > 0x1p-40 * d3(c[0], c[1], c[2], c[0], c[1], c[2])))
+        return false;                           // the cap plane is not normal to n
     Q16 near = q;
     for (int j = 0; j < 2; ++j) {
         Q16 far = near;
