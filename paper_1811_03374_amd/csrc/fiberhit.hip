@@ -1970,29 +1970,26 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
 // What bounds the end of a call is its longest pair: a trip of a wave alone on
 // its SIMD takes 0.7 to 1 us, and a few pairs in a million need a hundred and
 // more (degenerate ones up to 850). A trip with a rebuild takes two to three
-// times as long, so sharing starts once a wave has run 32 trips since its last
-// pair and takes place at every second trip (from 48 on 299,993 quadratic pairs
-// take 91 instead of 80 us; at every trip 83): a call whose longest
-// search ends soon after loses up to 11 us, others gain. Mean of 6 inputs,
-// without and with it: 2^20 mixed pairs at depth 22 343 -> 231 us, the quadratic
-// ones 122 -> 80, 99,991 mixed pairs at depth 16 94 -> 80, 500,009 refined
-// degenerate pairs 1249 -> 798. The trips are those of the loop for pairs of
-// their own: a second loop behind it cost every call 1 to 2 %.
+// times as long, and most searches end within a hundred trips: a wave starts to
+// share once it has run 96 since its last pair, at every second trip. Mean of 6
+// inputs of mixed pairs at depth 22, not shared, from 32 trips on, from 96 on:
+// 13,039 pairs 61.1, 74.3, 61.3 us; 40,000 72.2, 88.1, 72.6; 299,993 110, 126,
+// 110; 524,289 238, 171, 201; 2^20 266, 227, 238; 299,993 quadratic pairs 178,
+// 138, 163; 60,000 refined degenerate pairs 695, 344, 377. An input whose longest
+// search ends soon after sharing starts loses by it: of 16 inputs of 299,993
+// pairs the times against not sharing are 0.56 to 1.24 (five above 1.05), of 2^20
+// 0.33 to 1.09, of 40,000 1.00 to 1.15 (one above 1.03); from 32 trips on 40,000
+// pairs took 1.20 times as long on the whole. Waiting longer after helpers that
+// ended at once gained nothing (all calls 1 to 3 % slower).
+// The count of a call's pairs says nothing about its longest search: rules by
+// it (48 trips up to 2^16 pairs, 64 above 2^19) made 13,039 and 40,000 pairs 17 %
+// slower than not sharing. Nor do a wave's busy lanes: they are few by then (a
+// limit of 2, 4 or 8 changed nothing). The trips are those of the loop for pairs
+// of their own: a second loop behind it cost every call 1 to 2 %.
 #ifndef FIBERHIT_LONG_SEARCH
-#define FIBERHIT_LONG_SEARCH 32                // build knob: trips without a new pair after which searches are shared
+#define FIBERHIT_LONG_SEARCH 96                // build knob: trips without a new pair after which searches are shared
 #endif
 constexpr int kLongSearch = FIBERHIT_LONG_SEARCH;
-// Of few pairs the longest search is seldom much longer than that, and they wait
-// 48 trips: mixed pairs at depth 22, 4000 of them 61.6 -> 54.4 us (not shared
-// 57.3), 13,039 75.0 -> 70.1 (74.1), 40,000 87.2 -> 85.1 (86.4); at depth 15
-// 13,039 50.3 -> 48.1 (57.8) but 40,000 61.3 -> 63.5 (73.3), and 99,991 with
-// normals at depth 16 would lose (83 -> 88; 94).
-constexpr int64_t kSmallCall = 1 << 16;
-// In a large call other waves have the issue slots that a rebuild takes while
-// it is short of its end, and waves wait 64 trips: 2^20 mixed pairs at depth 22
-// whose longest search is short 215 -> 191 us (not shared 200 to 205), six other
-// inputs 216 -> 231 (343). 300,001 pairs take 130 us with 32 trips (196).
-constexpr int64_t kLargeCall = 1 << 19;
 
 struct Shared {                                // in LDS, where the queue was
     uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave];
@@ -2136,9 +2133,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     // hit counts if it is nearer than the one before)
     constexpr bool kShared = MODE != kCount && !CAND;
     Shared &sh = *(Shared *)s_queue;
-    // trips since the wave's last pair was started (from -16 or -32 on in a
-    // small or large call, see kSmallCall)
-    int tail = count <= kSmallCall ? -16 : count > kLargeCall ? -32 : 0;
+    int tail = 0;                        // trips since the wave's last pair was started
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
