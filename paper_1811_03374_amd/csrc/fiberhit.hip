@@ -1881,16 +1881,21 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
                                              int64_t begin, int64_t end, const float *aos, int *list, int *open)
 {
     const int lane = (int)threadIdx.x;
-    int scene0 = 0;
-    if constexpr (BATCHED) scene0 = find_scene(offsets, n_scenes, begin);
+    // batched: the scenes of the share, among which a pair's is searched by
+    // halves (2^20 hair pairs in 2^20 scenes: 626 us, one after another 927; in
+    // one scene 362)
+    int scene0 = 0, scenes_here = 1;
+    if constexpr (BATCHED) {
+        scene0 = find_scene(offsets, n_scenes, begin);
+        scenes_here = find_scene(offsets + scene0, n_scenes - scene0, end - 1) + 1;
+    }
     for (int64_t first = begin; first < end; first += kList) {
         const int size = end - first < kList ? (int)(end - first) : kList;
         // pair k of this part: its index in its scene, and the scene
         auto place = [&](int k, int &sc) {
             int64_t i = first + k;
             if constexpr (BATCHED) {
-                sc = scene0;
-                while (sc + 1 < n_scenes && offsets[sc + 1] <= i) ++sc;
+                sc = scene0 + find_scene(offsets + scene0, scenes_here, i);
                 i -= offsets[sc];
             }
             return i;
