@@ -2222,8 +2222,12 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                 float *f = &r.p.x;
 #pragma unroll
                 for (int k = 0; k < 16; ++k) f[k] = stage[k * kQueue];
+                // batched: the descriptor of the outputs is read again; held
+                // across the load of the pair it cost 3 spilled registers (128
+                // against 124 now; batches of 8 to 256 scenes 0 to 1.5 % faster)
+                const Args &o = BATCHED ? scenes[sc] : a0;
                 if (!ok) {
-                    if (!CAND) finish_invalid<MODE>(a, idx);
+                    if (!CAND) finish_invalid<MODE>(o, idx);
                 } else {
                     cap_interval(r, rtmax, rlo, rhi);
                     float te, tx, lu, hu;
@@ -2245,7 +2249,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                         D.level = 0;
                         D.trips = 1;
                         D.slack = slack;
-                        finish<MODE, CAND>(a, idx, D, vis, hit_geo(r, D.t, te < lu), Refined{}, round);
+                        finish<MODE, CAND>(o, idx, D, vis, hit_geo(r, D.t, te < lu), Refined{}, round);
                     }
                 }
             }
