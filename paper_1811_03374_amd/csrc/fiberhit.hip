@@ -1866,8 +1866,8 @@ __device__ __forceinline__ void wave_range(int64_t w, int64_t waves, int64_t cou
 // The FP64 decisions of a wave's pairs begin .. end - 1 that reached a leaf
 // (hit_out == kToRefine), once its traversal is done. The wave lists those
 // marked, up to kList pairs at a time, decides each with a lane of its own as
-// far as narrow_curve and simple_candidates go, lists what they leave open and
-// searches that, so that both passes run with full waves and no lane waits,
+// far as narrow_curve and simple_candidates go, lists what they leave open (over
+// the part of the list that has been read) and searches that, so that both passes run with full waves and no lane waits,
 // parked, for the last of its wave. Bound by FP64 arithmetic and, beside it, by
 // the longest pairs of the traversal, which the other waves' decisions hide: a
 // kernel of its own for the decisions was as fast on hair (409 against 399 us
@@ -1878,7 +1878,7 @@ constexpr int kList = 16 * kWave;              // pairs listed at a time
 
 template <bool BATCHED, bool QUAD>
 __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes, const int64_t *offsets, int n_scenes,
-                                             int64_t begin, int64_t end, const float *aos, int *list, int *open)
+                                             int64_t begin, int64_t end, const float *aos, int *list)
 {
     const int lane = (int)threadIdx.x;
     // batched: the scenes of the share, among which a pair's is searched by
@@ -1919,7 +1919,7 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
                 bool left = false;
                 int k = 0;
                 if (e0 + lane < todo) {
-                    k = (pass ? open : list)[e0 + lane];
+                    k = list[e0 + lane];
                     int sc = 0;
                     const int64_t i = place(k, sc);
                     const Args &a = BATCHED ? scenes[sc] : a0;
@@ -1952,7 +1952,7 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
                     }
                 }
                 const uint64_t m = __ballot(left);
-                if (left) open[n_open + (int)lanes_below(m)] = k;
+                if (left) list[n_open + (int)lanes_below(m)] = k;
                 n_open += __popcll(m);
             }
             __syncthreads();
@@ -2102,7 +2102,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
 {
     __shared__ float s_cache[16 * kWave];
     __shared__ float s_queue[kQWords * kQueue];
-    static_assert(sizeof(Shared) <= sizeof(s_queue) && kQWords * kQueue >= kList && 16 * kWave >= kList, "refine_range lists its pairs there");
+    static_assert(sizeof(Shared) <= sizeof(s_queue) && kQWords * kQueue >= kList, "refine_range lists its pairs there");
     const int lane = (int)threadIdx.x;
     float *col = s_cache + lane;
     const int64_t w = blockIdx.x, waves = gridDim.x;
@@ -2405,7 +2405,7 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         __threadfence_block();
         __syncthreads();
         wave_range(w, waves, count, next, end);
-        refine_range<BATCHED, QUAD>(*args, scenes, offsets, n_scenes, next, end, aos, (int *)s_cache, (int *)s_queue);
+        refine_range<BATCHED, QUAD>(*args, scenes, offsets, n_scenes, next, end, aos, (int *)s_queue);
     }
 }
 

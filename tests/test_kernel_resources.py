@@ -1,5 +1,6 @@
 """What the compiler gave the built kernels, read from the library's own code
-object (no GPU needed): the plain search kernels spill nothing."""
+object (no GPU needed): the plain search kernels spill nothing, and those
+without the parent cache leave its 4 KiB of LDS."""
 import os
 import re
 import shutil
@@ -64,3 +65,10 @@ def test_plain_kernels_spill_nothing(kernels):
         assert x["vgpr_count"] <= 128, key                   # four waves a SIMD
         if key[0] != 2:
             assert x["private_segment_fixed_size"] == 0 and x["vgpr_spill_count"] == 0, key
+
+
+@pytest.mark.parametrize("mode", [0, 2])
+def test_no_parent_cache_no_lds_for_it(kernels, mode):
+    f = fused(kernels)
+    cached, replayed = (f[mode, 1, 0, 0, pc]["group_segment_fixed_size"] for pc in (1, 0))
+    assert replayed == cached - 16 * 64 * 4
