@@ -515,9 +515,7 @@ __device__ __forceinline__ bool newton_surface(const Curve64 &c, double &t, doub
         t += dt;
         u += du;
         if (!(fabs(u) < 4.0) || !isfinite(t)) return false;
-        // (next to a cusp the steps are left to go on: where they end decides)
-        const double eps = c.regular ? 1e-15 : 4e-16;
-        if (fabs(du) <= eps && fabs(dt) <= eps * fabs(t)) break;
+        if (fabs(du) <= 4e-16 && fabs(dt) <= 4e-16 * fabs(t)) break;
     }
     double C[4], D[4], E[3];
     eval_curve(c, u, C, D, E);
