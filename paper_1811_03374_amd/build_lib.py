@@ -21,6 +21,11 @@ SRC = os.path.join(PKG, "csrc", "fiberhit.hip")
 SRCS = [SRC, os.path.join(PKG, "csrc", "presplit.hip")]
 OUT_DIR = os.path.join(PKG, "_lib")
 LIB = os.path.join(OUT_DIR, "libfiberhit.so")
+# the same sources with limits that large calls alone would meet set small, for
+# the tests of what happens there: nodes a wave of pre-subdivision stacks,
+# candidates of a list that one launch tests
+LIB_SMALL = os.path.join(OUT_DIR, "libfiberhit_small_limits.so")
+SMALL_LIMITS = ("-DFIBERHIT_NODE_STACK=64", "-DFIBERHIT_MAX_ROUNDS=3")
 ARCH = "gfx950"
 
 
@@ -32,18 +37,22 @@ def hipcc_cmd(out: str, extra=()):
             "-I", os.path.join(ROOT, "include"), *extra, "-o", out, *SRCS]
 
 
-def build(verbose: bool = False) -> str:
+def build(verbose: bool = False, lib: str = LIB, extra=()) -> str:
     os.makedirs(OUT_DIR, exist_ok=True)
-    tmp = LIB + ".tmp"
-    cmd = hipcc_cmd(tmp)
+    tmp = lib + ".tmp"
+    cmd = hipcc_cmd(tmp, extra)
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         sys.stderr.write(res.stdout + res.stderr)
         raise RuntimeError("hipcc failed")
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, lib)
+    return lib
+
+
+def build_small(verbose: bool = False) -> str:
+    return build(verbose, LIB_SMALL, SMALL_LIMITS)
 
 
 if __name__ == "__main__":

@@ -2082,7 +2082,11 @@ __device__ __forceinline__ bool first_leaf(bool &active, bool leaf, Shared &sh)
 #define FIBERHIT_READY 8                      // build knob: rays a setup round waits for
 #endif
 constexpr int kReady = FIBERHIT_READY;
-constexpr int32_t kMaxRounds = 1 << 24;        // candidates of a list a launch tests
+#ifndef FIBERHIT_MAX_ROUNDS
+#define FIBERHIT_MAX_ROUNDS (1 << 24)         // build knob: candidates of a list a launch tests
+#endif
+constexpr int32_t kMaxRounds = FIBERHIT_MAX_ROUNDS;
+static_assert(kMaxRounds <= 1 << 24, "a queue entry holds twice a candidate's number above 6 other bits");
 
 struct Waiting {                               // a ring
     int ray[2 * kWave], round[2 * kWave];

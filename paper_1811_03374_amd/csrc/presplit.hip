@@ -521,7 +521,11 @@ constexpr int kWave = 64;
 #ifndef FIBERHIT_NODE_STACK
 #define FIBERHIT_NODE_STACK 1024                // build knob: node stack entries of a wave
 #endif
+// The stack can fill: nodes that wait for a search come back as two halves
+// whatever its height, and 64 trees ten levels deep have reached 2038 entries
+// in a model of this order. What finds no room is walked by its own lane.
 constexpr int kStack = FIBERHIT_NODE_STACK;
+static_assert(kStack >= kWave, "the roots of a wave's fibers");
 constexpr int kMapWords = (1 << kMaxSplitLevel) / 32;
 
 template <int NF>                              // fibers a wave
