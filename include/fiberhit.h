@@ -24,11 +24,12 @@
  * for the subdivision search. The library allocates nothing while a call
  * runs. The only device memory a call needs beyond its inputs and outputs is
  * a copy of the fibers as 64-byte records for calls that gather fibers
- * through an index, in a workspace the caller sizes with
- * fiber_pairs_workspace_bytes; a batch needs its scene table, in a workspace
- * sized by fiber_batched_workspace_bytes, or inside a plan. Device set-up
- * (unit counts, occupancy, pinned staging of batched scene tables) happens
- * once per device, at fi_init_device or at the first call on that device.
+ * through an index (of more than 2^16 pairs, or candidate lists), in a
+ * workspace the caller sizes with fiber_pairs_workspace_bytes; a batch needs
+ * its scene table, in a workspace sized by fiber_batched_workspace_bytes, or
+ * inside a plan. Device set-up (unit counts, occupancy, pinned staging of
+ * batched scene tables) happens once per device, at fi_init_device or at the
+ * first call on that device.
  *
  * Layouts (structure of arrays, 32-bit floats, row-major):
  *   rays   : 7 rows of ray_stride floats  -- ox, oy, oz, dx, dy, dz, tmax.
@@ -110,8 +111,9 @@ int fi_init_device(void);
  * fiber_intersect_counts call of n_pairs pairs over a table of n_fibers
  * fibers can use: when gathered is non-zero (pair_fiber given) and
  * n_pairs >= n_fibers, the fibers' 64-byte records (tables up to 1 GiB);
- * otherwise 0. A call with a smaller workspace (or none) reads the fiber rows
- * in place, with the same results. flags is reserved. */
+ * otherwise 0. A call with a smaller workspace (or none), and one of at most
+ * 2^16 pairs whatever its workspace, reads the fiber rows in place, with the
+ * same results. flags is reserved. */
 size_t fiber_pairs_workspace_bytes(int64_t n_pairs, int64_t n_fibers, int32_t gathered, uint32_t flags);
 
 /*
@@ -221,17 +223,18 @@ int fiber_intersect_pairs(const float *rays, int64_t ray_stride, int64_t n_rays,
  *
  * Operation and arguments: those of fiber_intersect_pairs, minus the
  * workspace; the results are bit for bit the same. The fiber records of a
- * gathered call (pair_fiber given, n_pairs >= n_fibers) go to a fixed array
- * inside the library's code object (32 MiB, one copy per device, held until
- * the process ends; its address is taken once per device at the device's
- * set-up), which holds the records of up to 524,288 fibers: such a call over
- * a larger fiber table is refused with FI_ERR_SCRATCH before anything is
- * enqueued. Other calls use no scratch.
+ * gathered call (pair_fiber given, n_pairs >= n_fibers, n_pairs > 2^16) go to
+ * a fixed array inside the library's code object (32 MiB, one copy per device,
+ * held until the process ends; its address is taken once per device at the
+ * device's set-up), which holds the records of up to 524,288 fibers: such a
+ * call over a larger fiber table is refused with FI_ERR_SCRATCH before
+ * anything is enqueued. Other calls use no scratch.
  *
  * Every call on a device shares that device's array, which keeps the last
  * call's contents (a call writes the records it reads first, so nothing needs
- * clearing): gathered calls that overlap on one device -- on two streams, or
- * from two host threads without ordering -- race and give undefined results.
+ * clearing): such calls that overlap on one device -- on two streams, or from
+ * two host threads without ordering -- race and give undefined results. Calls
+ * of at most 2^16 pairs read the fiber rows and do not touch it.
  *
  * Allocation: none on the call path (no hipMalloc, hipFree or allocating
  * library routine). The device's set-up (fi_init_device, or the first call of

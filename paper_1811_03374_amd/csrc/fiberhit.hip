@@ -61,7 +61,7 @@ constexpr int kQWords = 21;                   // root node (16), lo, hi, tmax, p
 constexpr uint32_t kRootSize = 1u << 23;      // parametric domain [0, 1) in units of 2^-23
 constexpr uint32_t kStallBit = 1u << 31;       // flag bit kept in a lane's interval start
 constexpr uint32_t kStartMask = kRootSize - 1u;
-constexpr int kMaxTrips = 1 << 16;            // hang guard; real pairs need < 200 trips
+constexpr int kMaxTrips = 1 << 16;            // hang guard; the longest degenerate pairs seen need 850 trips
 #ifndef FIBERHIT_PARENT_CACHE
 #define FIBERHIT_PARENT_CACHE 1
 #endif
@@ -804,13 +804,15 @@ __device__ __forceinline__ bool simple_candidates(const Curve64 &c, const Part &
         const double low = fmin(fma(D[0], sx, D[1] * sy), fmin(fma(mx, sx, my * sy), fma(F[0], sx, F[1] * sy)));
         if (!(low > 0.0)) return false;
         const double dmin = low * low * __builtin_amdgcn_rcp(fma(sx, sx, sy * sy)) * 0.999999;
-        const double dmax = fmax(fma(D[0], D[0], D[1] * D[1]), fmax(fma(mx, mx, my * my), fma(F[0], F[0], F[1] * F[1])));
+        const double dmax = fmax(fma(D[0], D[0], D[1] * D[1]),
+                                 fmax(fma(mx, mx, my * my), fma(F[0], F[0], F[1] * F[1])));
         const double sg = copysign(1.0, D[2]), z = fmin(sg * D[2], fmin(sg * mz, sg * F[2]));
         const double R = part.reach;
         if (!(z > 0.0) || !(z * z >= 0x1p-20 * (dmax + z * z)) || !(4.0 * R * R * e2 <= dmin * dmin) ||
             !(16.0 * R * R * dmax * ez * ez <= dmin * dmin * z * z))
             return false;
-        const double er = fmax(fabs(c.q[2][3] - 2.0 * c.q[1][3] + c.q[0][3]), fabs(c.q[3][3] - 2.0 * c.q[2][3] + c.q[1][3]));
+        const double er = fmax(fabs(c.q[2][3] - 2.0 * c.q[1][3] + c.q[0][3]),
+                               fabs(c.q[3][3] - 2.0 * c.q[2][3] + c.q[1][3]));
         const double dr = fma(v, er, fmax(fabs(D[3]), fabs(F[3])));
         if (!(16.0 * dr * dr <= dmin) || !(8.0 * R * er <= dmin)) return false;
     }
@@ -1068,7 +1070,8 @@ struct Lane {
                                   // see stall_possible)
     uint32_t min_size;            // leaf size 2^(23 - depth)
     uint32_t cached;              // size of the pending children whose parent is cached (0: none)
-    int32_t waiting;              // refinement: parked at its first leaf until the wave decides it
+    int32_t waiting;              // refined candidate lists: parked at its first leaf until the wave
+                                  //   decides it
     float ru;                     //   the FP32 u of the leaf hit (Newton's start)
     int32_t scene;                // batched: the problem this pair belongs to
     int32_t pair;                 // index of the pair within its problem
@@ -1865,9 +1868,10 @@ __device__ __forceinline__ void wave_range(int64_t w, int64_t waves, int64_t cou
 // (hit_out == kToRefine), once its traversal is done. The wave lists those
 // marked, up to kList pairs at a time, decides each with a lane of its own as
 // far as narrow_curve and simple_candidates go, lists what they leave open (over
-// the part of the list that has been read) and searches that, so that both passes run with full waves and no lane waits,
-// parked, for the last of its wave. Bound by FP64 arithmetic and, beside it, by
-// the longest pairs of the traversal, which the other waves' decisions hide: a
+// the part of the list that has been read) and searches that, so that both
+// passes run with full waves and no lane waits, parked, for the last of its
+// wave. Bound by FP64 arithmetic and, beside it, by the longest pairs of the
+// traversal, which the other waves' decisions hide: a
 // kernel of its own for the decisions was as fast on hair (409 against 399 us
 // per 10^6 pairs) but waited for them (500,009 degenerate pairs 1.57 against
 // 1.14 ms). Before, with the lanes parked at their leaves and every pair
@@ -2104,7 +2108,8 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
 {
     __shared__ float s_cache[16 * kWave];
     __shared__ float s_queue[kQWords * kQueue];
-    static_assert(sizeof(Shared) <= sizeof(s_queue) && kQWords * kQueue >= kList, "refine_range lists its pairs there");
+    static_assert(sizeof(Shared) <= sizeof(s_queue) && kQWords * kQueue >= kList,
+                  "shared searches and refine_range's list take the queue's place");
     const int lane = (int)threadIdx.x;
     float *col = s_cache + lane;
     const int64_t w = blockIdx.x, waves = gridDim.x;
@@ -2549,7 +2554,9 @@ int device_info(DeviceInfo *&out)
 // Fiber records of a single call: when it gathers fibers through pair_fiber
 // and reads each fiber about once or more, the fibers are first copied to
 // 16-float records (one pass over the table): a gathered fiber is then one
-// or two cache lines instead of one line per coordinate row.
+// or two cache lines instead of one line per coordinate row. What the size
+// queries and the no-allocation entry point answer; a call of few pairs
+// (kRowPairs, see launch) leaves the room for them unused.
 size_t record_bytes(int64_t n_pairs, int64_t n_fibers, bool gathered)
 {
     const size_t need = (size_t)(n_fibers > 0 ? n_fibers : 0) * 16 * sizeof(float);
@@ -2646,12 +2653,12 @@ void remember_tuning(const fi_scene *sc, int32_t n, bool refine, const fi_tuning
 // was slower (overlapped 283 us), and so were twice the waves for deep
 // calls only (overlapped 250 us: the shallow call's waves then wait behind
 // the deep call's), a grid skewed towards the waves that start first on
-// each SIMD, and issue priority by progress through the share. The rounds
-// of candidate lists keep the resident waves: most of their pairs end at
-// the root, and twice the waves made them 15 % (refined 39 %) slower. Refined
-// calls keep them too: a wave lists its share's pairs for the FP64 decisions,
-// and longer lists fill its lanes better (hair 399 against 438 us per 10^6
-// pairs, 500,009 degenerate pairs 1.14 against 1.34 ms).
+// each SIMD, and issue priority by progress through the share. Candidate
+// lists keep the resident waves: twice as many changed six calls (3001 to
+// 524,288 lists, two of them refined) by -3 to +1 %. Refined calls keep them
+// too: a wave lists its share's pairs for the FP64 decisions, and longer lists
+// fill its lanes better (hair 399 against 438 us per 10^6 pairs, 500,009
+// degenerate pairs 1.14 against 1.34 ms).
 int64_t single_call_waves(const DeviceInfo &d, int mode, const Args &)
 {
     const bool cand = mode == kCandVariant || mode == kCandVariant + 1;
@@ -3066,8 +3073,8 @@ int fiber_batch_autotune(const fi_scene *scenes, int32_t n_scenes, uint32_t flag
     hipStream_t s = (hipStream_t)stream;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return FI_ERR_HIP;
-    // refining waves park lanes until the wave decides them together, so
-    // they refill early; plain waves refill late
+    // plain waves refill late; refining ones (which decide their pairs after
+    // their traversal) take the same time within 1 % with any of 1 to 56
     const int plain_refills[] = {32, 48, 56};
     const int refine_refills[] = {4, 8, 16};
     const int *refills = refine ? refine_refills : plain_refills;

@@ -5,8 +5,8 @@
 // Appendix B.2) and whose swept solid does not reach across a cap plane
 // (Section 3.4, the thick-fiber configuration of Fig. "EvilConfiguration").
 // Curves that fail must be split beforehand. These kernels run before the
-// per-pair test: one lane per fiber, all arithmetic in FP64 (a pass over
-// the fiber table, far from any hot loop).
+// per-pair test, all arithmetic in FP64 (passes over the fiber table, far from
+// any hot loop).
 //
 // Cap-plane excess (reading R17): the disc at u (centre C(u), radius r(u),
 // normal C'(u)) reaches furthest along a cap normal n at C(u) + r(u) m(u),
@@ -576,8 +576,9 @@ __device__ void walk_alone(WalkLds<NF> &s, const float *F, int64_t fs, int64_t i
         if (what == kSearch) {
             const int open = kThickBits & ~ends_clear(q);
             const double lim = 1e-9 * extent_of(q);
-            what = (open & 32 && largest_excess(q, false) > lim) || (open & 64 && largest_excess(q, true) > lim) ? kHalve
-                                                                                                             : kPiece;
+            const bool thick = (open & 32 && largest_excess(q, false) > lim) ||
+                               (open & 64 && largest_excess(q, true) > lim);
+            what = thick ? kHalve : kPiece;
         }
         if (what == kHalve) {
             ++level;                    // the left child
@@ -667,8 +668,8 @@ __device__ __forceinline__ int map_count(const WalkLds<NF> &s, int f, int max_le
 }
 
 template <int NF>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_presplit_count(const float *F, int64_t fs, int64_t n, int max_level,
-                                                          int64_t *counts)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void k_presplit_count(const float *F, int64_t fs, int64_t n, int max_level, int64_t *counts)
 {
     __shared__ WalkLds<NF> s;
     const int lane = (int)threadIdx.x;
@@ -683,10 +684,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8))) v
 // finding its piece in the bitmaps: consecutive lanes write consecutive
 // columns. A fiber with one piece is not walked again.
 template <int NF>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_presplit_write(const float *F, int64_t fs, int64_t n, int max_level,
-                                                          const int64_t *offsets, int64_t n_pieces, float *P,
-                                                          int64_t ps, int32_t *pfiber, float *pu0, float *pu1,
-                                                          int32_t *pmask)
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void k_presplit_write(const float *F, int64_t fs, int64_t n, int max_level, const int64_t *offsets, int64_t n_pieces,
+                      float *P, int64_t ps, int32_t *pfiber, float *pu0, float *pu1, int32_t *pmask)
 {
     __shared__ WalkLds<NF> s;
     __shared__ int s_before[NF];     // pieces of the fibers before each one
@@ -836,7 +836,8 @@ int fiber_validate(const float *fibers, int64_t fiber_stride, int64_t n_fibers, 
     // the excesses themselves need every search, the mask alone few
     const int own = excess_out ? kBlock / 2 : kBlock;
     hipLaunchKernelGGL(excess_out ? k_validate<true> : k_validate<false>,
-                       dim3((unsigned)((n_fibers + own - 1) / own)), dim3(kBlock), 0, (hipStream_t)stream, fibers, fiber_stride, n_fibers, mask_out, excess_out);
+                       dim3((unsigned)((n_fibers + own - 1) / own)), dim3(kBlock), 0, (hipStream_t)stream, fibers,
+                       fiber_stride, n_fibers, mask_out, excess_out);
     return hipGetLastError() == hipSuccess ? FI_OK : FI_ERR_HIP;
 }
 
@@ -862,7 +863,8 @@ int fiber_presplit_count(const float *fibers, int64_t fiber_stride, int64_t n_fi
     (void)hipGetLastError();
     const int nf = fibers_per_wave(n_fibers);
     hipLaunchKernelGGL(nf == 16 ? k_presplit_count<16> : k_presplit_count<64>,
-                       dim3((unsigned)((n_fibers + nf) / nf)), dim3(kWave), 0, s, fibers, fiber_stride, n_fibers, max_level, counts);
+                       dim3((unsigned)((n_fibers + nf) / nf)), dim3(kWave), 0, s, fibers, fiber_stride, n_fibers,
+                       max_level, counts);
     if (hipGetLastError() != hipSuccess) return FI_ERR_HIP;
     if (hipcub::DeviceScan::ExclusiveSum(temp, temp_bytes, counts, offsets_out, (int)(n_fibers + 1), s) !=
         hipSuccess)
@@ -882,8 +884,9 @@ int fiber_presplit(const float *fibers, int64_t fiber_stride, int64_t n_fibers, 
     (void)hipGetLastError();
     const int nf = fibers_per_wave(n_fibers);
     hipLaunchKernelGGL(nf == 16 ? k_presplit_write<16> : k_presplit_write<64>,
-                       dim3((unsigned)((n_fibers + nf - 1) / nf)), dim3(kWave), 0, (hipStream_t)stream, fibers, fiber_stride, n_fibers, max_level, offsets, n_pieces,
-                       pieces_out, piece_stride, piece_fiber, piece_u0, piece_u1, piece_mask);
+                       dim3((unsigned)((n_fibers + nf - 1) / nf)), dim3(kWave), 0, (hipStream_t)stream, fibers,
+                       fiber_stride, n_fibers, max_level, offsets, n_pieces, pieces_out, piece_stride, piece_fiber,
+                       piece_u0, piece_u1, piece_mask);
     return hipGetLastError() == hipSuccess ? FI_OK : FI_ERR_HIP;
 }
 
