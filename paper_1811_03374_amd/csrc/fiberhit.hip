@@ -2069,6 +2069,52 @@ __device__ __forceinline__ bool first_leaf(bool &active, bool leaf, Shared &sh)
     return leaf && order == first;
 }
 
+// A search of more than kMaxTrips trips is a miss, shared or not: what the lanes
+// of a wave spend on shared searches is bounded so that no pair can have taken
+// more, and a pair that is not decided by then starts again, alone. (Only
+// fibers so small that FP32 products underflow need so many: arcs of an extent
+// of 1e-6. Counted by each lane for itself, the limit let shared searches find
+// leaves behind it.)
+constexpr int kSharedTrips = kMaxTrips / 2;
+
+// Back into the queue, from its start: the pairs whose searches are still
+// shared (`active`: by this lane). Returns their number.
+__device__ __forceinline__ int stop_sharing(const Lane &L, bool active, Shared &sh, float *queue)
+{
+    const int lane = (int)threadIdx.x;
+    sh.stop[lane] = kWave;
+    __syncthreads();
+    if (active)
+        __hip_atomic_fetch_min(&sh.stop[sh.group[lane]], (uint32_t)lane, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    // lane g restores the pair that it had: its root, the rest from a lane that searches it
+    const bool again = sh.stop[lane] < (uint32_t)kWave;
+    const int from = again ? (int)sh.stop[lane] : lane;
+    const uint32_t start = __shfl(L.start, from), min_size = __shfl(L.min_size, from);
+    const int pair = __shfl(L.pair, from), scene = __shfl(L.scene, from);
+    const float tmax = __shfl(L.tmax, from);
+    Node r;
+    lds_get(sh.root + lane, r);
+    __syncthreads();
+    const uint64_t m = __ballot(again);
+    if (again) {
+        float lo, hi;
+        cap_interval(r, tmax, lo, hi);
+        float *q = queue + (int)lanes_below(m);
+        const float *f = &r.p.x;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) q[k * kQueue] = f[k];
+        q[16 * kQueue] = lo;
+        q[17 * kQueue] = hi;
+        q[18 * kQueue] = tmax;
+        q[19 * kQueue] = __int_as_float(pair);
+        q[20 * kQueue] = __int_as_float((scene << 6) | (start & kStallBit ? 32 : 0) | (__builtin_clz(min_size) - 8));
+    }
+    __syncthreads();
+    return __popcll(m);
+}
+
 // Candidate lists. A ray's candidates are tested one after another, each against
 // the ray shortened to its nearest hit so far; a wave keeps its rays from the
 // first candidate to the last. A ray whose search has ended waits, if its list
@@ -2146,6 +2192,10 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     constexpr bool kShared = MODE != kCount && !CAND;
     Shared &sh = *(Shared *)s_queue;
     int tail = 0;                        // trips since the wave's last pair was started
+    int spent = 0;                       // trips of its lanes while they share searches
+    // what `tail` becomes where the wave shares no more (at an odd distance
+    // from kLongSearch, where share_work does not run)
+    constexpr int kNeverShare = -(1 << 30) + 1 + (kLongSearch & 1);
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
@@ -2171,6 +2221,8 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                             if constexpr (BATCHED) finish<MODE>(scenes[L.scene], L.pair, L, false);
                             else finish<MODE>(a0, L.pair, L, false);
                         }
+                        // a search near the limit is left alone
+                        if (__ballot(active && L.trips > kMaxTrips - kSharedTrips) != 0) tail = kNeverShare;
                     }
                     if (((tail - kLongSearch) & 1) == 0) share_work(L, active, sh);
                 }
@@ -2342,7 +2394,17 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         const int st = trip<MODE, QUAD, PC, CAND>(L, root, col, hg);
         const bool done = active && st != kGoOn && !(MODE == kConservative && L.waiting);
         bool decides = done;
-        if (kShared && tail >= kLongSearch) decides = first_leaf(active, done && st == kHit, sh);
+        // (out of the common path: without the hints calls took 1 % longer)
+        if (kShared && __builtin_expect(tail >= kLongSearch, 0)) {
+            decides = first_leaf(active, done && st == kHit, sh);
+            spent += kWave - n_free;
+            if (__builtin_expect(spent > kSharedTrips - kWave, 0)) {
+                q_head = 0;
+                q_count = stop_sharing(L, active && !done, sh, s_queue);
+                active = false;
+                tail = kNeverShare;
+            }
+        }
         if (decides) {
             if constexpr (BATCHED) {
                 // lanes of the wave's current scene read its output
