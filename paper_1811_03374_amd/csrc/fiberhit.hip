@@ -1998,8 +1998,23 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
 #endif
 constexpr int kLongSearch = FIBERHIT_LONG_SEARCH;
 
+// A search of more than kMaxTrips trips is a miss, shared or not. The trips of a
+// group's lanes (`total`, added up as they end; those behind a leaf left out)
+// are at least what the search takes alone up to its leaf: a hit with no more
+// than the limit stands. With more it may or may not, and the wave runs its
+// share a second time, sharing nothing. (Counted by each lane for itself, the
+// limit let shared searches find leaves behind it: fibers so small that FP32
+// products underflow, arcs of an extent of 1e-6, need so many trips.) Until a wave
+// has spent kSharedTrips on shared searches no pair of it can have taken too
+// many, and nothing is looked at: calls take the same time as without the look
+// (a lane that starts its pair again by itself cost them 2 %, marked pairs
+// picked out of the share 1 %). The longest searches of 1.7 M degenerate pairs
+// (44,133 trips; 79.4 ms not shared) take 3.6 ms.
+constexpr int kSharedTrips = kMaxTrips / 2;
+constexpr uint32_t kMostShared = 16 * kMaxTrips;   // trips of a group's lanes after which it is given up
+
 struct Shared {                                // in LDS, where the queue was
-    uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave];
+    uint32_t order[kWave], group[kWave], stop[kWave], donor[kWave], total[kWave];
     float root[16 * kWave];                    // the groups' roots, in columns
 };
 
@@ -2009,6 +2024,7 @@ __device__ __forceinline__ void start_sharing(const Lane &L, Shared &sh)
     sh.order[lane] = 0;
     sh.group[lane] = lane;
     sh.stop[lane] = 0xffffffffu;
+    sh.total[lane] = 0;
     lds_put(sh.root + lane, L.root);
     __syncthreads();
 }
@@ -2069,50 +2085,22 @@ __device__ __forceinline__ bool first_leaf(bool &active, bool leaf, Shared &sh)
     return leaf && order == first;
 }
 
-// A search of more than kMaxTrips trips is a miss, shared or not: what the lanes
-// of a wave spend on shared searches is bounded so that no pair can have taken
-// more, and a pair that is not decided by then starts again, alone. (Only
-// fibers so small that FP32 products underflow need so many: arcs of an extent
-// of 1e-6. Counted by each lane for itself, the limit let shared searches find
-// leaves behind it.)
-constexpr int kSharedTrips = kMaxTrips / 2;
-
-// Back into the queue, from its start: the pairs whose searches are still
-// shared (`active`: by this lane). Returns their number.
-__device__ __forceinline__ int stop_sharing(const Lane &L, bool active, Shared &sh, float *queue)
+// Once a wave has spent kSharedTrips on shared searches: may this lane's search
+// have met the trip limit before its leaf? `done`: it has ended in this trip. A
+// group ends with such a lane, or is given up and its lanes end.
+__device__ __forceinline__ bool unsure_search(bool &active, bool done, Shared &sh)
 {
     const int lane = (int)threadIdx.x;
-    sh.stop[lane] = kWave;
+    sh.donor[lane] = 0;
     __syncthreads();
-    if (active)
-        __hip_atomic_fetch_min(&sh.stop[sh.group[lane]], (uint32_t)lane, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_WORKGROUP);
+    const uint32_t group = sh.group[lane], total = sh.total[group];
+    const bool cut = active && total > kMostShared;
+    if (active && !done && !cut) sh.donor[group] = 1;         // the group goes on
     __syncthreads();
-    // lane g restores the pair that it had: its root, the rest from a lane that searches it
-    const bool again = sh.stop[lane] < (uint32_t)kWave;
-    const int from = again ? (int)sh.stop[lane] : lane;
-    const uint32_t start = __shfl(L.start, from), min_size = __shfl(L.min_size, from);
-    const int pair = __shfl(L.pair, from), scene = __shfl(L.scene, from);
-    const float tmax = __shfl(L.tmax, from);
-    Node r;
-    lds_get(sh.root + lane, r);
+    const bool over = done && sh.stop[group] != 0xffffffffu && total > (uint32_t)kMaxTrips && sh.donor[group] == 0;
     __syncthreads();
-    const uint64_t m = __ballot(again);
-    if (again) {
-        float lo, hi;
-        cap_interval(r, tmax, lo, hi);
-        float *q = queue + (int)lanes_below(m);
-        const float *f = &r.p.x;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) q[k * kQueue] = f[k];
-        q[16 * kQueue] = lo;
-        q[17 * kQueue] = hi;
-        q[18 * kQueue] = tmax;
-        q[19 * kQueue] = __int_as_float(pair);
-        q[20 * kQueue] = __int_as_float((scene << 6) | (start & kStallBit ? 32 : 0) | (__builtin_clz(min_size) - 8));
-    }
-    __syncthreads();
-    return __popcll(m);
+    if (cut) active = false;
+    return cut || over;
 }
 
 // Candidate lists. A ray's candidates are tested one after another, each against
@@ -2192,10 +2180,9 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
     constexpr bool kShared = MODE != kCount && !CAND;
     Shared &sh = *(Shared *)s_queue;
     int tail = 0;                        // trips since the wave's last pair was started
-    int spent = 0;                       // trips of its lanes while they share searches
-    // what `tail` becomes where the wave shares no more (at an odd distance
-    // from kLongSearch, where share_work does not run)
-    constexpr int kNeverShare = -(1 << 30) + 1 + (kLongSearch & 1);
+    int spent = 0;                       // trips of its lanes while they share searches,
+    uint64_t unsure = 0;                 //   and whether one may have met the trip limit
+    constexpr int kNeverShare = -(1 << 30);                            // what `tail` becomes then
     for (;;) {
         const uint64_t free_mask = __ballot(!active);
         const int n_free = __popcll(free_mask);
@@ -2221,8 +2208,8 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
                             if constexpr (BATCHED) finish<MODE>(scenes[L.scene], L.pair, L, false);
                             else finish<MODE>(a0, L.pair, L, false);
                         }
-                        // a search near the limit is left alone
-                        if (__ballot(active && L.trips > kMaxTrips - kSharedTrips) != 0) tail = kNeverShare;
+                        // a search near the limit already
+                        if (__ballot(active && L.trips > kMaxTrips - kSharedTrips) != 0) spent = kSharedTrips;
                     }
                     if (((tail - kLongSearch) & 1) == 0) share_work(L, active, sh);
                 }
@@ -2397,12 +2384,26 @@ void k_fused(Args a0, const Args *scenes, const int64_t *offsets, int n_scenes, 
         // (out of the common path: without the hints calls took 1 % longer)
         if (kShared && __builtin_expect(tail >= kLongSearch, 0)) {
             decides = first_leaf(active, done && st == kHit, sh);
+            if (done && (active || decides))
+                __hip_atomic_fetch_add(&sh.total[sh.group[lane]], (uint32_t)L.trips, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
             spent += kWave - n_free;
             if (__builtin_expect(spent > kSharedTrips - kWave, 0)) {
-                q_head = 0;
-                q_count = stop_sharing(L, active && !done, sh, s_queue);
-                active = false;
-                tail = kNeverShare;
+                unsure |= __ballot(unsure_search(active, done, sh));
+                if (unsure != 0 && __ballot(active && !done) == 0) {
+                    // the wave's share again
+                    wave_range(w, waves, count, next, end);
+                    left = (int)(end - next);
+                    q_head = 0;
+                    tail = kNeverShare;
+                    spent = 0;
+                    if constexpr (BATCHED) {
+                        scene0 = __builtin_amdgcn_readfirstlane(find_scene(offsets, n_scenes, next));
+                        uniform_scene(scenes[scene0], cur);
+                        base0 = uniform_i64(offsets[scene0]);
+                        bound0 = uniform_i64(offsets[scene0 + 1]);
+                    }
+                }
             }
         }
         if (decides) {
