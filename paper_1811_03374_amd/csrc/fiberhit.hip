@@ -1986,8 +1986,12 @@ __device__ __forceinline__ void refine_range(const Args &a0, const Args *scenes,
 // search ends soon after sharing starts loses by it: of 16 inputs of 299,993
 // pairs the times against not sharing are 0.56 to 1.24 (five above 1.05), of 2^20
 // 0.33 to 1.09, of 40,000 1.00 to 1.15 (one above 1.03); from 32 trips on 40,000
-// pairs took 1.20 times as long on the whole. Waiting longer after helpers that
-// ended at once gained nothing (all calls 1 to 3 % slower).
+// pairs took 1.20 times as long on the whole: 5 % for the start, next to nothing
+// for one hand-over, the rest for one at every second trip. Hand-overs 8, 16 or
+// 32 trips apart from 32, 48 or 64 on and at every second trip from 96 or 128 on
+// gained nothing against 96 (51 calls, 6 inputs, against not sharing at all:
+// 0.964 of the time with 96, 0.964 to 0.993 with those), nor did waiting longer
+// after helpers that ended at once (all calls 1 to 3 % slower).
 // The count of a call's pairs says nothing about its longest search: rules by
 // it (48 trips up to 2^16 pairs, 64 above 2^19) made 13,039 and 40,000 pairs 17 %
 // slower than not sharing. Nor do a wave's busy lanes: they are few by then (a
