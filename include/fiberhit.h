@@ -40,7 +40,9 @@
  *
  * Per-pair data that make a pair meaningless (a zero, infinite or NaN
  * direction, a NaN tmax, an index outside its array, a per-pair depth above
- * 23) are not errors: that pair is reported as a miss.
+ * 23) are not errors: that pair is reported as a miss. So is a pair whose
+ * search takes more than 65,536 node tests (the count is that of the search by
+ * one lane, however many shared it).
  */
 #ifndef FIBERHIT_H
 #define FIBERHIT_H
